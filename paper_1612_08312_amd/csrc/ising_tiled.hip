@@ -417,8 +417,9 @@ hipError_t launch_ising_energy_tail(const Chain &c, hipStream_t st, const Launch
 // issue-bound passes (tile, flip) of some run beside the latency-bound
 // passes (unite, store) of others on the same compute units.
 //
-// Visibility between phases: after an item its writes are released to agent
-// scope (L2 written back) before the completed count is raised; a waiting
+// Visibility between phases: after an item every wave waits for its stores,
+// then its writes are released to agent scope (L2 written back) before the
+// completed count is raised; a waiting
 // item acquires at agent scope (caches invalidated) after the count is
 // reached.  Every wait is bounded: past kPersistSpin polls the error flag is
 // raised and every workgroup leaves (the host reports the error).
@@ -519,6 +520,10 @@ __global__ __launch_bounds__(TX *TY *TZ) void k_persist_ising(Chain c, int *ctl)
         else if (phase == 1) unite_tile<NC>(d, tile, tid, S.unite);
         else if (phase == 2) store_tile<NC>(d, st, tile, tid, S.HK);
         else ising_flip_pass<TX, TY, TZ>(d, st, tile, tid, S.flip);
+        // The barrier alone orders LDS only: a wave's stores (labels, crossing
+        // lists, spins) may still be on their way to the L2 when it passes, and
+        // thread 0's release would not write them back.
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         int *q = persist_ctl(ctl, r);
         if (phase == 3) {
