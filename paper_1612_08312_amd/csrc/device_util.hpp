@@ -9,6 +9,16 @@ namespace pyro {
 
 constexpr int kWave = 64;
 
+// LDS written by lanes of a wave before it is read by the wave's other lanes
+// after it: the LDS serves a wave's accesses in order, so only the compiler
+// has to keep them so.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Product of non-negative a, b below 2^24 (every lattice index product:
 // L <= 406, so cell indices stay below 2^27) on the full-rate 24-bit
 // multiplier; a 32-bit integer multiply is a quarter-rate instruction.

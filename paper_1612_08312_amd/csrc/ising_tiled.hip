@@ -40,8 +40,8 @@ namespace pyro {
 template <int TX, int TY, int TZ>
 struct IsingTileLds {
     uint32_t P[kForestSlots<TX * TY * TZ>];     // tile forest
-    uint32_t SM[TX * TY * TZ];                  // spin masks of the cells
-    uint32_t U[kIsingUnionsPerCell<TX * TY * TZ> * TX * TY * TZ];  // union list
+    uint16_t SM[TX * TY * TZ];                  // spin masks of the cells
+    uint32_t U[kUnionWords<TX * TY * TZ>];      // union buffers
     uint8_t K4[64];
     int64_t red[16];
 };
@@ -59,8 +59,8 @@ template <int TX, int TY, int TZ, bool kLast = false>
 __device__ __forceinline__ void ising_tile_pass(const RepDesc &d, const RepState &st, int tile, int tid,
                                                 IsingTileLds<TX, TY, TZ> &S)
 {
-    constexpr int NC = TX * TY * TZ;
-    uint32_t *P = S.P, *SM = S.SM, *U = S.U;
+    uint32_t *P = S.P, *U = S.U;
+    uint16_t *SM = S.SM;
     uint8_t *K4 = S.K4;
     int64_t *red = S.red;
     const TileIdx<TX, TY, TZ> ti = TileIdx<TX, TY, TZ>::of(tile, d);
@@ -78,7 +78,7 @@ __device__ __forceinline__ void ising_tile_pass(const RepDesc &d, const RepState
     }
     uint32_t m = 0;
     if (valid) m = spin_mask16(reinterpret_cast<const int4 *>(s)[cell]);
-    SM[lcid] = m;
+    SM[lcid] = (uint16_t)m;
     __syncthreads();
 
     uint64_t act = 0;
@@ -114,7 +114,7 @@ __device__ __forceinline__ void ising_tile_pass(const RepDesc &d, const RepState
         aligned_count = (int)__popcll(al);
         act = ising_activate(al, (uint32_t)cell, st.t, d.key, IsingParams{d.thr_hi, d.thr_lo});
     }
-    tile_components<TX, TY, TZ, kIsingUnionsPerCell<NC>>(d, ti, tile, tid, lcid, valid, cell, act, lc, P, U, SM, K4);
+    tile_components<TX, TY, TZ>(d, ti, tile, tid, lcid, valid, cell, act, lc, P, U, K4);
     const int64_t bsum = block_sum<int64_t, !kLast>(valid ? (int64_t)(2 * aligned_count - nbonds) : 0, red);
     if (tid == 0) d.ipart[tile] = bsum;
 }

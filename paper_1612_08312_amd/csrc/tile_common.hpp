@@ -38,14 +38,6 @@ __device__ __forceinline__ uint32_t node_off(int key)
     return 4u * (uint32_t)(key + (key >> 4));
 }
 
-// Key of the node at byte offset off: slot - slot / 17, the quotient by a
-// 24-bit multiply and shift (exact for every slot below 2^16).
-__device__ __forceinline__ int node_key(uint32_t off)
-{
-    const uint32_t slot = off >> 2, c = __umul24(slot, 61681u) >> 20;
-    return (int)(slot - c);
-}
-
 // Entry at byte offset off of the forest array, addressed in the LDS
 // address space (a 32-bit offset, no generic-pointer arithmetic).
 typedef __attribute__((address_space(3))) volatile uint32_t lds_word;
@@ -629,30 +621,25 @@ __host__ __device__ constexpr uint64_t down_vertex_bytes(int half)
 }
 
 // ------------------------------------------------------ tile components ---
-// Union-list entries per cell of a tile of NC cells (the UPC argument of
-// tile_components); unions beyond the list are done by the thread that
-// found them.  The Ising tile pass keeps one entry per cell for tiles of
-// 512 cells or more: the smaller list lets four 8x8x8 tile workgroups share
-// a CU's LDS instead of three, which pays more than the balance of a longer
-// list (tile pass 598 -> 569 us per launch over five L = 128 lattices).
-// Its smaller tiles keep eight (one per cell made L = 48 sweeps with 8x8x4
-// tiles 3-4% slower), and so does the O(n) tile pass, whose 8x8x8 tiles
-// were 3-4% slower with one.
+// LDS words of the union buffers of a tile's waves (the U argument of
+// tile_components): 128 per wave, one word per union, and room for one more
+// row of 64 while a full one is united.  Later they hold two words per cell.
 template <int NC>
-constexpr int kIsingUnionsPerCell = NC >= 512 ? 1 : 8;
-constexpr int kOnUnionsPerCell = 8;
+constexpr int kUnionWords = 2 * NC;
 
 // Second half of both models' tile pass (every thread of the block calls
 // it; `act` is 0 for threads without a cell, lc[] holds the local index of
-// each neighbour cell of the thread's cell, or -1 outside the tile; DA is
-// LDS for one word per cell): the components of the tile's sites from the
-// active bonds of its cells, written as every site's tile-local root, and
-// the tile's crossing list.
+// each neighbour cell of the thread's cell, or -1 outside the tile): the
+// components of the tile's sites from the active bonds of its cells, written
+// as every site's tile-local root, and the tile's crossing list.
 //
 // Inside the tile, each down tetrahedron contributes the spanning edges of
 // the components of its active bonds whose two ends lie in the tile (at most
-// 3, from the K4 table); all threads then process the tile's list of such
-// unions evenly, so one busy cell does not hold up its wave.
+// 3, from the K4 table).  A wave collects its cells' unions (about 330 at
+// T_c) in an LDS buffer of its own and unites them 64 at a time, one per
+// lane, as the buffer fills, with no barrier: united in place by the cells
+// that find them, a third to a half of the lanes sit idle in each of the
+// twelve slots.
 //
 // Every site is a vertex of exactly one down tetrahedron, owned by one cell,
 // so the crossing bonds of different cells never join the same pair of
@@ -663,128 +650,112 @@ constexpr int kOnUnionsPerCell = 8;
 // whose name differs are emitted: at most 3 pairs per tetrahedron, none
 // repeated.  These tetrahedra belong to the cells of the low faces; they
 // are handed out to all threads as a table of (cell, tetrahedron) items.
-template <int TX, int TY, int TZ, int UPC>
+template <int TX, int TY, int TZ>
 __device__ __forceinline__ void tile_components(const RepDesc &d, const TileIdx<TX, TY, TZ> &ti, int tile, int tid,
                                                 int lcid, bool valid, int cell, uint64_t act,
-                                                const int (&lc)[kNCellCodes], uint32_t *P, uint32_t *U, uint32_t *DA,
+                                                const int (&lc)[kNCellCodes], uint32_t *P, uint32_t *U,
                                                 const uint8_t *K4)
 {
     constexpr int NC = TX * TY * TZ;
     static_assert(NC % 64 == 0, "tiles are whole waves");
-    constexpr int kCap = UPC * NC - NC / 64;  // union list; its wave totals follow it in U
-    uint32_t *WT = U + kCap;
-    // local key of vertex mu of down tetrahedron f (-1 when outside the tile)
-    auto vkey = [&](int f, int mu) {
-        const SiteRef R = down_vertex(f, mu);
-        const int l = R.cell == kSelf ? lcid : lc[R.cell];
-        return l >= 0 ? 16 * l + R.site : -1;
-    };
+    const int lane = tid & 63, wave = tid >> 6;
+    const uint32_t base = node_off(16 * lcid);
     // Up tetrahedra: components from the table, roots at the smallest vertex.
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
         const uint32_t code = K4[(uint32_t)(act >> (6 * f)) & 63u];
-        const uint32_t base = node_off(16 * lcid + 4 * f);
 #pragma unroll
-        for (int mu = 0; mu < 4; ++mu) node(P, base + 4 * mu) = base + 4 * ((code >> (2 * mu)) & 3);
+        for (int mu = 0; mu < 4; ++mu) node(P, base + 4 * (4 * f + mu)) = base + 4 * (4 * f + ((code >> (2 * mu)) & 3));
     }
-    // No barrier here: the down tetrahedra below read only registers and K4,
-    // and the forest is first read after the barrier of the list placement.
+    __syncthreads();
     // Down tetrahedra, inside the tile: spanning edges, packed as two 16-bit
-    // forest slots (17 NC < 2^16).
-    uint32_t un[12];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) un[k] = 0xFFFFFFFFu;  // no union (also for threads without a cell)
-    unsigned nun = 0;
-    if (valid) {
+    // forest slots (17 NC < 2^16 up to 8x8x8; 17 bits are never needed, the
+    // largest slot of a 1024-cell tile is 17407).
+    {
+        const int s0 = 17 * lcid;
+        auto slot_of = [&](int f, int mu) {  // slot of a vertex (used only when it lies in the tile)
+            const SiteRef R = down_vertex(f, mu);
+            return (R.cell == kSelf ? s0 : 17 * lc[R.cell]) + R.site;
+        };
+        auto in_tile = [&](int f, int mu) {
+            const SiteRef R = down_vertex(f, mu);
+            return R.cell == kSelf || lc[R.cell] >= 0;
+        };
+        lds_word *W = (lds_word *)((lds_byte *)U + 512 * wave);
+        int c = 0;  // unions in the buffer (wave uniform, below 64 between slots)
+        auto unite_row = [&](int n) {  // the first n <= 64 unions of the buffer, one per lane
+            wave_sync();
+            if (lane < n) {
+                const uint32_t u = W[lane];
+                lds_unite(P, (u >> 14) & ~3u, (u & 0xFFFFu) << 2);
+            }
+        };
 #pragma unroll
         for (int f = 0; f < 4; ++f) {
-            const int k0 = vkey(f, 0), k1 = vkey(f, 1), k2 = vkey(f, 2), k3 = vkey(f, 3);
             uint32_t inside = 0;  // bonds with both ends in the tile
 #pragma unroll
-            for (int e = 0; e < 6; ++e) {
-                const int a = pair_a(e), b = pair_b(e);
-                const int ka = a == 0 ? k0 : (a == 1 ? k1 : k2), kb = b == 1 ? k1 : (b == 2 ? k2 : k3);
-                inside |= (uint32_t)(ka >= 0 && kb >= 0) << e;
-            }
+            for (int e = 0; e < 6; ++e) inside |= (uint32_t)(in_tile(f, pair_a(e)) && in_tile(f, pair_b(e))) << e;
             const uint32_t code = K4[(uint32_t)(act >> (24 + 6 * f)) & inside];
+            const int k0 = slot_of(f, 0), k1 = slot_of(f, 1), k2 = slot_of(f, 2), k3 = slot_of(f, 3);
 #pragma unroll
             for (int mu = 1; mu < 4; ++mu) {
-                const int rp = (code >> (2 * mu)) & 3;
-                const int kr = rp == 0 ? k0 : (rp == 1 ? k1 : k2);
+                const uint32_t rp = (code >> (2 * mu)) & 3u;
+                const int kr = mu == 1 || rp == 0 ? k0 : (mu == 2 || rp == 1 ? k1 : k2);
                 const int km = mu == 1 ? k1 : (mu == 2 ? k2 : k3);
-                const bool use = rp != mu;
-                un[3 * f + mu - 1] = use ? (node_off(kr) << 14 | node_off(km) >> 2) : 0xFFFFFFFFu;
-                nun += use;
+                const bool use = rp != (uint32_t)mu;
+                const uint64_t b = __ballot(use);
+                const int at = c + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+                if (use) W[at] = (uint32_t)kr << 16 | (uint32_t)km;
+                c += (int)__popcll(b);
+                if (c >= 64) {
+                    unite_row(64);
+                    const uint32_t rest = W[64 + lane];
+                    wave_sync();
+                    W[lane] = rest;
+                    wave_sync();
+                    c -= 64;
+                }
             }
         }
+        unite_row(c);
     }
-    // The thread's unions go after those of the lanes below it (four ballots
-    // of its 0..12 count) and of the lower waves (totals in WT, past the
-    // list's room in U; DA may still be read by a slower thread's bond
-    // activation, which is why it does not hold them).
-    uint32_t below = 0, wtot = 0;
+    __syncthreads();
+    // Tile-local roots of the thread's sites, all sixteen walks a level at a
+    // time (parents never exceed children, so the walks end): as global site
+    // indices into the labels, and into the forest entries, where the
+    // emission below reads the root of any site of the tile.  The global
+    // index of slot s = 17 c + k is s plus a word of its cell c, kept in U
+    // (free after the unions).
+    uint32_t r[16];
 #pragma unroll
-    for (int bit = 0; bit < 4; ++bit) {
-        const uint64_t b = __ballot((nun >> bit) & 1u);
-        below += __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u)) << bit;
-        wtot += (uint32_t)__popcll(b) << bit;
-    }
-    const int wave = tid >> 6;
-    if ((tid & 63) == 0) WT[wave] = wtot;
-    __syncthreads();
-    int ntotal = 0;
-    unsigned at = below;
-    for (int w = 0; w < NC / 64; ++w) {
-        const int t = (int)WT[w];
-        at += w < wave ? t : 0;
-        ntotal += t;
-    }
-    if (nun) {
-#pragma unroll
-        for (int k = 0; k < 12; ++k) {
-            if (un[k] == 0xFFFFFFFFu) continue;
-            if (at < (unsigned)kCap) U[at] = un[k];
-            else lds_unite(P, (un[k] >> 14) & ~3u, (un[k] & 0xFFFFu) << 2);
-            ++at;
-        }
-    }
-    __syncthreads();
-    // Each thread takes a contiguous run of the list: a cell's unions sit
-    // together in it, so the lanes of a wave work on different cells' roots.
-    {
-        const int nlist = min(ntotal, kCap);
-        const int per = (nlist + NC - 1) / NC;
-        const int kb = min(tid * per, nlist), ke = min(kb + per, nlist);
-        for (int k = kb; k < ke; ++k) lds_unite(P, (U[k] >> 14) & ~3u, (U[k] & 0xFFFFu) << 2);
-    }
-    __syncthreads();
-    // Tile-local roots of the thread's sites, as global site indices: into
-    // the labels, and into the forest entries, where the emission below
-    // reads the root of any site of the tile.  A key's global index is the
-    // base of its row (a table in U, free after the unions) plus its offset
-    // in the row, 16 lx + k.
-    static_assert((TX & (TX - 1)) == 0 && TX * TY * TZ <= 1024, "power-of-two rows");
-    constexpr int kRowShift = 4 + (TX == 4 ? 2 : (TX == 8 ? 3 : 4));
-    for (int row = tid; row < TY * TZ; row += NC) U[row] = (uint32_t)ti.row_base(row);
-    int r[16];
-    if (valid) {
-        const uint32_t base = node_off(16 * lcid);
-#pragma unroll
-        for (int k = 0; k < 16; ++k) r[k] = node_key(lds_find(P, base + 4 * k));
-    }
-    __syncthreads();
-    if (valid) {
-        const uint32_t base = node_off(16 * lcid);
+    for (int k = 0; k < 16; ++k) r[k] = node(P, base + 4 * k);
+    uint32_t moved;
+    do {
+        moved = 0;
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-            r[k] = (int)U[(uint32_t)r[k] >> kRowShift] + (r[k] & (16 * TX - 1));
-            node(P, base + 4 * k) = (uint32_t)r[k];
+            const uint32_t p = node(P, r[k]);
+            moved |= p ^ r[k];
+            r[k] = p;
         }
+    } while (moved);
+    U[lcid] = (uint32_t)(16 * cell - 17 * lcid);
+    uint32_t *DA = U + NC;  // active bonds of the cells' down tetrahedra
+    DA[lcid] = (uint32_t)(act >> 24);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        // cell of the root's slot: offset / 68 (unsigned: past 2^31 for 16x8x8 tiles, below 2^32)
+        const uint32_t c = (uint32_t)__umul24(r[k], 61681u) >> 22;
+        r[k] = U[c] + (r[k] >> 2);
+        node(P, base + 4 * k) = r[k];
+    }
+    if (valid) {
         int4 *out = reinterpret_cast<int4 *>(d.label + 16 * cell);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) out[q] = make_int4(r[4 * q], r[4 * q + 1], r[4 * q + 2], r[4 * q + 3]);
+        for (int q = 0; q < 4; ++q)
+            out[q] = make_int4((int)r[4 * q], (int)r[4 * q + 1], (int)r[4 * q + 2], (int)r[4 * q + 3]);
     }
-    DA[lcid] = (uint32_t)(act >> 24);  // active bonds of the cell's down tetrahedra
     __syncthreads();
     // Crossing pairs, one item (cell, down tetrahedron) per thread and round.
     // Each round places its pairs in item order: a lane's offset is the
