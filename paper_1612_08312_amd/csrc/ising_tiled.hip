@@ -11,7 +11,8 @@
 //                  and list the tile's crossing pairs (tile_components).  The
 //                  parallel-bond count is the energy of the incoming state.
 //   k_forest      unite pass over the crossing lists (tile_common.hpp): the
-//                  global forest over the tiles' local roots.
+//                  global forest over the tiles' local roots, and the record
+//                  of the previous sweep.
 //   k_settle_flip_ising  one workgroup per tile: settle the tile's hooked
 //                  local roots (their cluster's smallest site and flip
 //                  coin), then the coin of every site's cluster from an LDS
@@ -19,8 +20,6 @@
 //                  flip of the int8 spins, magnetisation of the new state.
 //                  (The persistent kernel runs the store pass of
 //                  tile_common.hpp and ising_flip_pass instead.)
-//   k_finalize_ising  fixed-order sums of the partials into the records,
-//                  then advance the replica's state.
 // Local site order inside a tile follows the global order, so a tile-local
 // root is the smallest site index of its local component, and the canonical
 // passes make every label the smallest site index of its cluster.
@@ -39,10 +38,15 @@ namespace pyro {
 // LDS of the tile pass and of the flip of one tile.
 template <int TX, int TY, int TZ>
 struct IsingTileLds {
+    // spin masks: the tile's cells, then the cells one step down across its
+    // low faces x, y, z and low edges yz, xz, xy
+    static constexpr int kX = TX * TY * TZ, kY = kX + TY * TZ, kZ = kY + TX * TZ, kYZ = kZ + TX * TY, kXZ = kYZ + TX,
+                         kXY = kXZ + TY, kMasks = kXY + TZ;
     uint32_t P[kForestSlots<TX * TY * TZ>];     // tile forest
-    uint16_t SM[TX * TY * TZ];                  // spin masks of the cells
+    uint16_t SM[kMasks];
     uint32_t U[kUnionWords<TX * TY * TZ>];      // union buffers
     uint8_t K4[64];
+    uint32_t NB[8];  // port words of the neighbouring tiles
     int64_t red[16];
 };
 
@@ -64,7 +68,7 @@ __device__ __forceinline__ void ising_tile_pass(const RepDesc &d, const RepState
     uint8_t *K4 = S.K4;
     int64_t *red = S.red;
     const TileIdx<TX, TY, TZ> ti = TileIdx<TX, TY, TZ>::of(tile, d);
-    const int8_t *__restrict__ s = (const int8_t *)d.spins;
+    constexpr int NC = TX * TY * TZ;
     const int L = d.L;
     const int lcid = tid;  // local cell of the thread
     const int lx = lcid % TX, ly = (lcid / TX) % TY, lz = lcid / (TX * TY);
@@ -76,34 +80,46 @@ __device__ __forceinline__ void ising_tile_pass(const RepDesc &d, const RepState
         constexpr K4Table k4 = make_k4();
         K4[tid] = k4.v[tid];
     }
-    uint32_t m = 0;
-    if (valid) m = spin_mask16(reinterpret_cast<const int4 *>(s)[cell]);
+    using Lds = IsingTileLds<TX, TY, TZ>;
+    const int4 *__restrict__ s4 = reinterpret_cast<const int4 *>(d.spins);
+    // Each cell's mask is formed once, the halo's by the first threads beside
+    // their own (every lane had formed all six of its neighbours outside the
+    // tile: 72 of 1521 vector instructions).
+    static_assert(Lds::kMasks - NC <= NC, "one halo cell per thread");
+    int4 own = make_int4(0, 0, 0, 0), halo = make_int4(0, 0, 0, 0);
+    if (valid) own = s4[cell];
+    if (tid < Lds::kMasks - NC) {
+        const int j = tid + NC;
+        const int i = j - (j < Lds::kY ? Lds::kX : j < Lds::kZ ? Lds::kY : j < Lds::kYZ ? Lds::kZ : j < Lds::kXZ ? Lds::kYZ
+                                                                     : j < Lds::kXY ? Lds::kXZ : Lds::kXY);
+        const bool fx = j < Lds::kY, fy = !fx && j < Lds::kZ, fz = !fx && !fy && j < Lds::kYZ;
+        const bool eyz = j >= Lds::kYZ && j < Lds::kXZ, exz = j >= Lds::kXZ && j < Lds::kXY, exy = j >= Lds::kXY;
+        const int x0 = ti.bx * TX, y0 = ti.by * TY, z0 = ti.bz * TZ;
+        const int xm = x0 == 0 ? L - 1 : x0 - 1, ym = y0 == 0 ? L - 1 : y0 - 1, zm = z0 == 0 ? L - 1 : z0 - 1;
+        const int hx = fx || exz || exy ? xm : x0 + (eyz ? i : i % TX);
+        const int hy = fy || eyz || exy ? ym : y0 + (fx ? i % TY : fz ? i / TX : i);
+        const int hz = fz || eyz || exz ? zm : z0 + (fx ? i / TY : fy ? i / TX : i);
+        if (hx < L && hy < L && hz < L) halo = s4[cell_index(hx, hy, hz, L)];
+        SM[j] = (uint16_t)spin_mask16(halo);
+    }
+    const uint32_t m = spin_mask16(own);
     SM[lcid] = (uint16_t)m;
     __syncthreads();
 
     uint64_t act = 0;
     int aligned_count = 0, nbonds = 48;
     int lc[kNCellCodes];
-#pragma unroll
-    for (int q = 0; q < kNCellCodes; ++q) lc[q] = -1;
+    ti.local_neighbours(d, lx, ly, lz, lcid, lc);
     if (valid) {
-        NbrCell nb[kNCellCodes];
-        ti.neighbours(x, y, z, cell, lcid, nb);
-        // Spins of the neighbour cells outside the tile: every lane issues all
-        // six loads (its own cell, a cache hit, where the neighbour is in the
-        // tile), so they are in flight together instead of one divergent
-        // branch at a time.
-        int4 gv[kNCellCodes];
-#pragma unroll
-        for (int q = 1; q < kNCellCodes; ++q)
-            gv[q] = reinterpret_cast<const int4 *>(s)[nb[q].lcell >= 0 ? cell : nb[q].gcell];
+        const int iX = lx > 0 ? lcid - 1 : Lds::kX + lcid / TX, iY = ly > 0 ? lcid - TX : Lds::kY + lz * TX + lx,
+                  iZ = lz > 0 ? lcid - TX * TY : Lds::kZ + lcid % (TX * TY);
         uint32_t nm[kNCellCodes];
-        nm[kSelf] = m;
-#pragma unroll
-        for (int q = 0; q < kNCellCodes; ++q) {
-            lc[q] = nb[q].lcell;
-            if (q > 0) nm[q] = nb[q].lcell >= 0 ? SM[nb[q].lcell] : spin_mask16(gv[q]);
-        }
+        nm[kMx] = SM[iX];
+        nm[kMy] = SM[iY];
+        nm[kMz] = SM[iZ];
+        nm[kMyMz] = SM[ly > 0 ? iZ - TX : (lz > 0 ? iY - TX : Lds::kYZ + lx)];
+        nm[kMxMz] = SM[lx > 0 ? iZ - 1 : (lz > 0 ? iX - TY : Lds::kXZ + ly)];
+        nm[kMxMy] = SM[lx > 0 ? iY - 1 : (ly > 0 ? iX - 1 : Lds::kXY + lz)];
         const uint32_t dm = down_mask16(m, nm[kMx], nm[kMy], nm[kMz], nm[kMyMz], nm[kMxMz], nm[kMxMy]);
         uint64_t al = aligned48(m, dm);
         if (d.present) {  // a bond with a vacant end is neither a candidate nor counted in E
@@ -114,8 +130,9 @@ __device__ __forceinline__ void ising_tile_pass(const RepDesc &d, const RepState
         aligned_count = (int)__popcll(al);
         act = ising_activate(al, (uint32_t)cell, st.t, d.key, IsingParams{d.thr_hi, d.thr_lo});
     }
-    tile_components<TX, TY, TZ>(d, ti, tile, tid, lcid, valid, cell, act, lc, P, U, K4);
-    const int64_t bsum = block_sum<int64_t, !kLast>(valid ? (int64_t)(2 * aligned_count - nbonds) : 0, red);
+    tile_components<TX, TY, TZ>(d, ti, tile, tid, lcid, valid, cell, act, lc, P, U, K4, S.NB);
+    // at most 48 per cell and 1024 cells: 32 bits
+    const int bsum = block_sum<int, !kLast>(valid ? 2 * aligned_count - nbonds : 0, (int *)red);
     if (tid == 0) d.ipart[tile] = bsum;
 }
 
@@ -191,7 +208,7 @@ __device__ __forceinline__ void ising_flip_pass(const RepDesc &d, const RepState
     __syncthreads();
     int mag = 0;
     if (valid) mag = flip_cell(d.spins, cell, cell_flip_mask<NC>(lab, LAB, CB, ti, cell, tid, st.t, d.key));
-    const int64_t msum = block_sum<int64_t>((int64_t)mag, red);
+    const int msum = block_sum<int>(mag, (int *)red);
     if (tid == 0) d.ipart[d.mpart_off + tile] = msum;
 }
 
@@ -238,7 +255,7 @@ __device__ __forceinline__ void ising_settle_flip_pass(const RepDesc &d, const R
         else flipmask = cell_flip_mask<NC>(lab, LAB, CB, ti, cell, tid, st.t, d.key);
         mag = flip_cell(d.spins, cell, flipmask);
     }
-    const int64_t msum = block_sum<int64_t, false>((int64_t)mag, S.f.red);
+    const int msum = block_sum<int, false>(mag, (int *)S.f.red);
     if (tid == 0) d.ipart[d.mpart_off + tile] = msum;
 }
 
@@ -248,9 +265,10 @@ __global__ __launch_bounds__(TX *TY *TZ) void k_settle_flip_ising(Chain c)
     __shared__ IsingSettleLds<TX, TY, TZ> S;
     const int blk = blockIdx.x;
     const int rep = c.tile_rep[blk];
-    const RepState st = *c.state[rep];
+    const RepState st = c.state[rep][1];
     if (st.remaining <= 0) return;
     const RepDesc &d = c.desc[rep];
+    if (blk == d.tile_base && threadIdx.x == 0) advance_state(c.state[rep], st, d);
     if constexpr (TX % 8 == 0) {
         if (d.lgL >= 0) {
             ising_settle_flip_pass<TX, TY, TZ, kFlipPow2>(d, st, blk - d.tile_base, threadIdx.x, S);
@@ -262,60 +280,6 @@ __global__ __launch_bounds__(TX *TY *TZ) void k_settle_flip_ising(Chain c)
         }
     }
     ising_settle_flip_pass<TX, TY, TZ, kFlipGeneral>(d, st, blk - d.tile_base, threadIdx.x, S);
-}
-
-// Records and state: energy partials (state before this sweep) into the
-// pending record, magnetisation of the new state into a new record (a block
-// of NT threads; the sums are exact integers).
-template <int NT>
-__device__ __forceinline__ void ising_finalize(const RepDesc &d, const RepState &st, RepState *stp, int tid,
-                                               int64_t *red)
-{
-    const int ntiles = d.ntx * d.nty * d.ntz;
-    int64_t E = 0, M = 0;
-    for (int k = tid; k < ntiles; k += NT) {
-        E += d.ipart[k];
-        M += d.ipart[d.mpart_off + k];
-    }
-    E = block_sum<int64_t>(E, red);
-    M = block_sum<int64_t>(M, red);
-    if (tid == 0) {
-        if (st.e_pending >= 0) {
-            d.ring[st.e_pending].bond_sum = E;
-            d.ring[st.e_pending].E = -d.J * (double)E;
-        }
-        const int slot = st.ring_used;
-        if (slot < d.ring_cap) {
-            DevRecord r;
-            r.sweep = st.t;
-            r.bond_sum = 0;
-            r.M_int = M;
-            r.reserved = 0;
-            r.E = 0.0;
-            r.M[0] = (double)M;
-            r.M[1] = 0.0;
-            r.M[2] = 0.0;
-            const double mm = (double)M / (double)d.N;
-            r.m2 = mm * mm;
-            r.m4 = r.m2 * r.m2;
-            d.ring[slot] = r;
-        }
-        RepState ns;
-        ns.t = st.t + 1;
-        ns.remaining = st.remaining - 1;
-        ns.ring_used = slot + 1;
-        ns.e_pending = slot < d.ring_cap ? slot : -1;
-        *stp = ns;
-    }
-}
-
-__global__ __launch_bounds__(kFinalizeThreads) void k_finalize_ising(Chain c)
-{
-    __shared__ int64_t red[16];
-    const int rep = blockIdx.x;
-    const RepState st = *c.state[rep];
-    if (st.remaining <= 0) return;
-    ising_finalize<kFinalizeThreads>(c.desc[rep], st, c.state[rep], threadIdx.x, red);
 }
 
 // Energy of the current state for replicas whose last record is pending.
@@ -349,24 +313,6 @@ __global__ __launch_bounds__(kBlock) void k_energy_ising(Chain c)
     if (threadIdx.x == 0) d.ipart[d.tail_off + blk] = bsum;
 }
 
-__global__ __launch_bounds__(kBlock) void k_energy_tail_finalize_ising(Chain c)
-{
-    __shared__ int64_t red[16];
-    const int rep = blockIdx.x;
-    const RepState st = *c.state[rep];
-    if (st.e_pending < 0) return;
-    const RepDesc &d = c.desc[rep];
-    const int ncb = blocks_for(d.ncell);
-    int64_t E = 0;
-    for (int k = threadIdx.x; k < ncb; k += blockDim.x) E += d.ipart[d.tail_off + k];
-    E = block_sum<int64_t>(E, red);
-    if (threadIdx.x == 0) {
-        d.ring[st.e_pending].bond_sum = E;
-        d.ring[st.e_pending].E = -d.J * (double)E;
-        c.state[rep]->e_pending = -1;
-    }
-}
-
 struct IsingLocal {
     template <int TX, int TY, int TZ>
     static hipError_t run(const Chain &c, hipStream_t st, const LaunchHook &hook)
@@ -390,16 +336,13 @@ hipError_t launch_ising_sweep(const Chain &c, hipStream_t st, const LaunchHook &
     hipError_t e = with_tile_shape<IsingLocal>(c.shape, c, st, hook);
     if (e == hipSuccess) e = launch_unite(c, st, hook);
     if (e == hipSuccess) e = with_tile_shape<IsingFlip>(c.shape, c, st, hook);
-    if (e != hipSuccess) return e;
-    PYRO_LAUNCH(kKFinalize, k_finalize_ising, c.nreps, kFinalizeThreads, c);
-    return hipSuccess;
+    return e;
 }
 
 hipError_t launch_ising_energy_tail(const Chain &c, hipStream_t st, const LaunchHook &hook)
 {
     PYRO_LAUNCH(kKEnergy, k_energy_ising, c.ncell_blocks, kBlock, c);
-    PYRO_LAUNCH(kKFinalize, k_energy_tail_finalize_ising, c.nreps, kBlock, c);
-    return hipSuccess;
+    return launch_pending_records(c, true, st, hook);
 }
 
 // ------------------------------------------------ persistent fused sweep ---
@@ -443,6 +386,46 @@ __global__ void k_persist_reset(Chain c, int *ctl)
     q[2] = 0;
     q[3] = S;
     q[4] = 4 * S * d.ntx * d.nty * d.ntz;
+}
+
+// Records and state after a sweep: energy partials (state before this sweep)
+// into the pending record, magnetisation of the new state into a new record
+// (a block of NT threads; the sums are exact integers).
+template <int NT>
+__device__ __forceinline__ void ising_finalize(const RepDesc &d, const RepState &st, RepState *stp, int tid,
+                                               int64_t *red)
+{
+    const int ntiles = d.ntx * d.nty * d.ntz;
+    int64_t E = 0, M = 0;
+    for (int k = tid; k < ntiles; k += NT) {
+        E += d.ipart[k];
+        M += d.ipart[d.mpart_off + k];
+    }
+    E = block_sum<int64_t>(E, red);
+    M = block_sum<int64_t>(M, red);
+    if (tid == 0) {
+        if (st.e_pending >= 0) {
+            d.ring[st.e_pending].bond_sum = E;
+            d.ring[st.e_pending].E = -d.J * (double)E;
+        }
+        const int slot = st.ring_used;
+        if (slot < d.ring_cap) {
+            DevRecord r;
+            r.sweep = st.t;
+            r.bond_sum = 0;
+            r.M_int = M;
+            r.reserved = 0;
+            r.E = 0.0;
+            r.M[0] = (double)M;
+            r.M[1] = 0.0;
+            r.M[2] = 0.0;
+            const double mm = (double)M / (double)d.N;
+            r.m2 = mm * mm;
+            r.m4 = r.m2 * r.m2;
+            d.ring[slot] = r;
+        }
+        advance_state(stp, st, d);
+    }
 }
 
 __device__ __forceinline__ int ld_agent(const int *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -548,8 +531,10 @@ struct IsingPersist {
     template <int TX, int TY, int TZ>
     static hipError_t run(const Chain &c, int *ctl, int grid, hipStream_t st, const LaunchHook &hook)
     {
+        hipError_t e = launch_pending_records(c, false, st, hook);
+        if (e != hipSuccess) return e;
         k_persist_reset<<<blocks_for(c.nreps), kBlock, 0, st>>>(c, ctl);
-        hipError_t e = hipGetLastError();
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
         PYRO_LAUNCH(kKPersist, (k_persist_ising<TX, TY, TZ>), grid, TX * TY * TZ, c, ctl);
         return hipSuccess;

@@ -6,8 +6,8 @@
 // of its run) and a small mutable state (sweep index, sweeps still to run,
 // record ring position) that lives in device memory, so that one captured
 // graph can replay sweeps for any set of replicas: the kernels read the
-// sweep index and skip replicas with nothing left to run, and the last
-// kernel of a sweep advances the state.
+// sweep index and skip replicas with nothing left to run, and each sweep
+// advances the state.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -21,14 +21,13 @@ namespace pyro {
 // return `status`.
 int record_error(int status, const char *msg);
 
-// Record layout written by the finalize kernels; identical to pyro_sw_record.
+// Record layout written on the device; identical to pyro_sw_record.
 struct DevRecord {
     int64_t sweep, bond_sum, M_int, reserved;
     double E, M[3], m2, m4;
 };
 
 constexpr int kBlock = 256;  // threads of the per-cell and per-call kernels
-constexpr int kFinalizeThreads = 1024;  // one workgroup per replica sums its partials
 
 __host__ __device__ inline int blocks_for(int64_t n, int per_block = kBlock) { return (int)((n + per_block - 1) / per_block); }
 
@@ -76,14 +75,29 @@ struct RepState {
     uint32_t t;         // global index of the next sweep
     int32_t remaining;  // sweeps still to run in the current call
     int32_t ring_used;  // records in the ring
-    int32_t e_pending;  // ring slot whose energy is not reduced yet, or -1
+    int32_t e_pending;  // ring slot of the last sweep's record while its sums are not reduced yet, or -1
 };
+
+// Each replica has two states side by side.  The tile pass and the unite
+// pass of a sweep read the first; a block of the unite pass copies it to the
+// second, which the settle-and-flip pass reads while its first block advances
+// the first for the next sweep.  No kernel reads a state that it changes, and
+// no kernel of its own is needed to advance it.
+// The word after them is the number of magnetisation partials that pass left
+// (the tile shape may change before they are summed).
+constexpr int kStateSlots = 3;  // room of a replica's states and that word
+__device__ inline int &mag_partials(RepState *s) { return *reinterpret_cast<int *>(s + 2); }
+
+__host__ __device__ inline RepState advanced(const RepState &s, int ring_cap)
+{
+    return RepState{s.t + 1, s.remaining - 1, s.ring_used + 1, s.ring_used < ring_cap ? s.ring_used : -1};
+}
 
 // What every chain kernel receives: descriptors, states and the block ->
 // replica maps of the two grids.
 struct Chain {
     const RepDesc *desc;
-    RepState *const *state;  // state of each replica (in its own workspace)
+    RepState *const *state;  // the two states of each replica (in its own workspace)
     const int *tile_rep;  // tile grid
     const int *cblk_rep;  // 256-cell blocks
     int nreps;

@@ -58,6 +58,7 @@ __global__ __launch_bounds__(TX *TY *TZ) __attribute__((amdgpu_waves_per_eu(4)))
     __shared__ uint32_t P[kForestSlots<NC>];
     __shared__ uint32_t U[kUnionWords<NC>];
     __shared__ uint8_t K4[64];
+    __shared__ uint32_t NB[8];
     __shared__ double red[16];
 
     const int blk = blockIdx.x;
@@ -84,19 +85,15 @@ __global__ __launch_bounds__(TX *TY *TZ) __attribute__((amdgpu_waves_per_eu(4)))
 
     uint64_t act = 0;
     double esum = 0.0;
-    int lc[kNCellCodes];
-    NbrCell nb[kNCellCodes];
+    int lc[kNCellCodes], gc[kNCellCodes];
+    ti.local_neighbours(d, lx, ly, lz, lcid, lc);
+    ti.global_neighbours(x, y, z, cell, gc);
     float own[NV][16];
-#pragma unroll
-    for (int q = 0; q < kNCellCodes; ++q) lc[q] = -1;
 #pragma unroll
     for (int k = 0; k < NV; ++k)
 #pragma unroll
         for (int q = 0; q < 16; ++q) own[k][q] = 0.0f;
     if (valid) {
-        ti.neighbours(x, y, z, cell, lcid, nb);
-#pragma unroll
-        for (int q = 0; q < kNCellCodes; ++q) lc[q] = nb[q].lcell;
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             const float4 *S4 = reinterpret_cast<const float4 *>(s + (int64_t)k * N) + 4 * (int64_t)cell;
@@ -133,7 +130,7 @@ __global__ __launch_bounds__(TX *TY *TZ) __attribute__((amdgpu_waves_per_eu(4)))
                     } else {
                         const int l = lc[R.cell];
                         if (l >= 0) v = SP[R.site * NC + l];
-                        else v = s[(int64_t)k * N + 16 * nb[R.cell].gcell + R.site];
+                        else v = s[(int64_t)k * N + 16 * gc[R.cell] + R.site];
                     }
                     dv[k][4 * f + mu] = v;
                 }
@@ -185,7 +182,7 @@ __global__ __launch_bounds__(TX *TY *TZ) __attribute__((amdgpu_waves_per_eu(4)))
             }
         }
     }
-    tile_components<TX, TY, TZ>(d, ti, tile, tid, lcid, valid, cell, act, lc, P, U, K4);
+    tile_components<TX, TY, TZ>(d, ti, tile, tid, lcid, valid, cell, act, lc, P, U, K4, NB);
     const double b = block_sum<double, false>(esum, red);
     if (tid == 0) d.dpart[tile] = b;
 }
@@ -286,9 +283,10 @@ __global__ __launch_bounds__(TX *TY *TZ) void k_settle_flip_on(Chain c)
 {
     __shared__ OnFlipLds<TX, TY, TZ> S;
     const int rep = c.tile_rep[blockIdx.x];
-    const RepState st = *c.state[rep];
+    const RepState st = c.state[rep][1];
     if (st.remaining <= 0) return;
     const RepDesc &d = c.desc[rep];
+    if ((int)blockIdx.x == d.tile_base && threadIdx.x == 0) advance_state(c.state[rep], st, d);
     if constexpr (TX % 8 == 0) {
         if (d.lgL >= 0) {
             on_settle_flip_pass<NV, TX, TY, TZ, kFlipPow2>(d, st, blockIdx.x - d.tile_base, threadIdx.x, S);
@@ -300,59 +298,6 @@ __global__ __launch_bounds__(TX *TY *TZ) void k_settle_flip_on(Chain c)
         }
     }
     on_settle_flip_pass<NV, TX, TY, TZ, kFlipGeneral>(d, st, blockIdx.x - d.tile_base, threadIdx.x, S);
-}
-
-// Records and state (see k_finalize_ising).
-template <int NV>
-__global__ __launch_bounds__(kFinalizeThreads) void k_finalize_on(Chain c)
-{
-    __shared__ double red[16 * (1 + NV)];
-    const int rep = blockIdx.x;
-    const RepState st = *c.state[rep];
-    if (st.remaining <= 0) return;
-    const RepDesc &d = c.desc[rep];
-    const int ntiles = d.ntx * d.nty * d.ntz;
-    // the energy and the NV magnetisation sums, each in the order of one
-    // block_sum of its own: their loads go out together and one barrier
-    // serves all of them
-    double v[1 + NV];
-#pragma unroll
-    for (int q = 0; q <= NV; ++q) v[q] = 0.0;
-    for (int k = threadIdx.x; k < ntiles; k += blockDim.x) {
-        v[0] += d.dpart[k];
-#pragma unroll
-        for (int q = 0; q < NV; ++q) v[1 + q] += d.dpart[d.mpart_off * (1 + q) + k];
-    }
-    block_sum_n<double, 1 + NV>(v, red);
-    const double E = v[0];
-    double M[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-    for (int q = 0; q < NV; ++q) M[q] = v[1 + q];
-    if (threadIdx.x == 0) {
-        if (st.e_pending >= 0) d.ring[st.e_pending].E = -d.J * E;
-        const int slot = st.ring_used;
-        if (slot < d.ring_cap) {
-            DevRecord rec;
-            rec.sweep = st.t;
-            rec.bond_sum = 0;
-            rec.M_int = 0;
-            rec.reserved = 0;
-            rec.E = 0.0;
-            rec.M[0] = M[0];
-            rec.M[1] = M[1];
-            rec.M[2] = M[2];
-            const double m = sqrt(M[0] * M[0] + M[1] * M[1] + M[2] * M[2]) / (double)d.N;
-            rec.m2 = m * m;
-            rec.m4 = rec.m2 * rec.m2;
-            d.ring[slot] = rec;
-        }
-        RepState ns;
-        ns.t = st.t + 1;
-        ns.remaining = st.remaining - 1;
-        ns.ring_used = slot + 1;
-        ns.e_pending = slot < d.ring_cap ? slot : -1;
-        *c.state[rep] = ns;
-    }
 }
 
 // Energy of the current state for replicas whose last record is pending.
@@ -384,23 +329,6 @@ __global__ __launch_bounds__(kBlock) void k_energy_on(Chain c)
     if (threadIdx.x == 0) d.dpart[d.tail_off + blk] = b;
 }
 
-__global__ __launch_bounds__(kBlock) void k_energy_tail_finalize_on(Chain c)
-{
-    __shared__ double red[16];
-    const int rep = blockIdx.x;
-    const RepState st = *c.state[rep];
-    if (st.e_pending < 0) return;
-    const RepDesc &d = c.desc[rep];
-    const int ncb = blocks_for(d.ncell);
-    double E = 0.0;
-    for (int k = threadIdx.x; k < ncb; k += blockDim.x) E += d.dpart[d.tail_off + k];
-    E = block_sum<double>(E, red);
-    if (threadIdx.x == 0) {
-        d.ring[st.e_pending].E = -d.J * E;
-        c.state[rep]->e_pending = -1;
-    }
-}
-
 template <int NV>
 struct OnLocal {
     template <int TX, int TY, int TZ>
@@ -427,9 +355,7 @@ static hipError_t sweep_on(const Chain &c, hipStream_t st, const LaunchHook &hoo
     hipError_t e = with_tile_shape<OnLocal<NV>>(c.shape, c, st, hook);
     if (e == hipSuccess) e = launch_unite(c, st, hook);
     if (e == hipSuccess) e = with_tile_shape<OnFlip<NV>>(c.shape, c, st, hook);
-    if (e != hipSuccess) return e;
-    PYRO_LAUNCH(kKFinalize, k_finalize_on<NV>, c.nreps, kFinalizeThreads, c);
-    return hipSuccess;
+    return e;
 }
 
 hipError_t launch_on_sweep(const Chain &c, hipStream_t st, const LaunchHook &hook)
@@ -441,8 +367,7 @@ template <int NV>
 static hipError_t energy_tail_on(const Chain &c, hipStream_t st, const LaunchHook &hook)
 {
     PYRO_LAUNCH(kKEnergy, k_energy_on<NV>, c.ncell_blocks, kBlock, c);
-    PYRO_LAUNCH(kKFinalize, k_energy_tail_finalize_on, c.nreps, kBlock, c);
-    return hipSuccess;
+    return launch_pending_records(c, true, st, hook);
 }
 
 hipError_t launch_on_energy_tail(const Chain &c, hipStream_t st, const LaunchHook &hook)

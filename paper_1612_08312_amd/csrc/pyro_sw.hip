@@ -149,7 +149,7 @@ Layout layout_for(int L, int model)
     ly.dpart = take(model == PYRO_ISING ? 0 : sizeof(double) * (size_t)dpart_count(L));
     ly.ring = take(sizeof(pyro_sw_record) * (size_t)kRing);
     ly.pairs = take(sizeof(int) * (size_t)pair_list_ints(L));
-    ly.state = take(sizeof(RepState));
+    ly.state = take(kStateSlots * sizeof(RepState));
     ly.solo_desc = take(sizeof(RepDesc));
     ly.solo_stp = take(sizeof(RepState *));
     ly.map_len = std::max<int64_t>(max_tiles(L), blocks_for(ncell));

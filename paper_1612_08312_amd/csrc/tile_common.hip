@@ -27,8 +27,28 @@ __global__ __launch_bounds__(kBlock) void k_canonical_labels(const int32_t *__re
 
 hipError_t launch_unite(const Chain &c, hipStream_t st, const LaunchHook &hook)
 {
-    if (c.counts) PYRO_LAUNCH(kKUnite, k_forest<true>, c.ntile_blocks, kUniteThreads, c);
-    else PYRO_LAUNCH(kKUnite, k_forest<false>, c.ntile_blocks, kUniteThreads, c);
+    if (c.counts) PYRO_LAUNCH(kKUnite, k_forest<true>, c.ntile_blocks + c.nreps, kUniteThreads, c);
+    else PYRO_LAUNCH(kKUnite, k_forest<false>, c.ntile_blocks + c.nreps, kUniteThreads, c);
+    return hipSuccess;
+}
+
+// Complete the pending record of every replica that has one: after the energy
+// tail (with_energy), or, before a persistent launch overwrites the
+// magnetisation partials, all but its energy, which that launch adds.
+__global__ __launch_bounds__(kBlock) void k_pending_records(Chain c, bool with_energy)
+{
+    __shared__ double red[16 * 4];
+    const int rep = blockIdx.x;
+    const RepState st = c.state[rep][0];
+    if (st.e_pending < 0) return;
+    const RepDesc &d = c.desc[rep];
+    write_pending_record(d, c.model, st, mag_partials(c.state[rep]), threadIdx.x, with_energy, d.tail_off, blocks_for(d.ncell), red);
+    if (with_energy && threadIdx.x == 0) c.state[rep]->e_pending = -1;
+}
+
+hipError_t launch_pending_records(const Chain &c, bool with_energy, hipStream_t st, const LaunchHook &hook)
+{
+    PYRO_LAUNCH(kKFinalize, k_pending_records, c.nreps, kBlock, c, with_energy);
     return hipSuccess;
 }
 
@@ -62,13 +82,15 @@ static int64_t max_tiles(int L)
 }
 
 int64_t max_tile_count(int L) { return max_tiles(L); }
-// A tile's crossing list holds at most 3 pairs for each of the 4 down
-// tetrahedra of each of its low-face cells.
+// A tile's crossing list holds at most 3 pairs for each tetrahedron that can
+// leave it, about half of what 4 tetrahedra for each of its low-face cells
+// would need; the port words at the end of the stride take less than the
+// other half.  A multiple of four words keeps them aligned.
 int tile_list_stride(int shape)
 {
     const TileDims t = tile_dims(shape);
     const int face = t.x * t.y * t.z - (t.x - 1) * (t.y - 1) * (t.z - 1);
-    return 2 + 2 * 12 * face;
+    return (2 + 2 * 12 * face) / 4 * 4;
 }
 
 int64_t pair_list_ints(int L)

@@ -105,11 +105,6 @@ __device__ __forceinline__ int lds_pos(int key)
     return (int)(((unsigned)key & 15u) * NC + ((unsigned)key >> 4));
 }
 
-struct NbrCell {
-    int gcell;  // global cell index
-    int lcell;  // local cell index in the tile, or -1 if outside
-};
-
 // Quotient a / b for 0 <= a < 2^24 and b >= 1 with a small quotient: a
 // float reciprocal gives it to within one, an integer check corrects it.
 __device__ __forceinline__ int small_div(int a, int b, float inv_b)
@@ -138,22 +133,6 @@ struct TileIdx {
         t.inv_L = 1.0f / (float)t.L;
         t.inv_LL = 1.0f / (float)(t.L * t.L);
         return t;
-    }
-    __device__ __forceinline__ NbrCell at(int x, int y, int z) const
-    {
-        NbrCell c;
-        c.gcell = cell_index(x, y, z, L);
-        const int tx = x - bx * TX, ty = y - by * TY, tz = z - bz * TZ;
-        const bool in = (unsigned)tx < (unsigned)TX && (unsigned)ty < (unsigned)TY && (unsigned)tz < (unsigned)TZ;
-        c.lcell = in ? (tz * TY + ty) * TX + tx : -1;
-        return c;
-    }
-    // Global site index of the first site of local row `row` = lz TY + ly of
-    // the tile (its cells x = bx TX .. bx TX + TX - 1 are consecutive).
-    __device__ __forceinline__ int row_base(int row) const
-    {
-        const int lz = row / TY, ly = row % TY;
-        return 16 * (base + mul24(mul24(lz, L) + ly, L));
     }
     // Global site index of local key l = 16 c + k.
     __device__ __forceinline__ int global_site(int l) const
@@ -189,18 +168,34 @@ struct TileIdx {
         const int dx = r1 - __mul24(dy, L);
         return 16 * (lcell + dx + dy * TX + dz * (TX * TY)) + (site & 15);
     }
-    // The seven cells the bonds of cell (x, y, z) touch (periodic wrap).
-    __device__ __forceinline__ void neighbours(int x, int y, int z, int cell, int lcell,
-                                              NbrCell nb[kNCellCodes]) const
+    // Local indices of the seven cells the bonds of local cell (lx, ly, lz)
+    // touch, -1 outside the tile.  Only an axis with a single tile wraps onto
+    // the tile itself, whose last cell on it is its extent less one.
+    __device__ __forceinline__ void local_neighbours(const RepDesc &d, int lx, int ly, int lz, int lcell,
+                                                     int (&lc)[kNCellCodes]) const
     {
-        const int xm = x == 0 ? L - 1 : x - 1, ym = y == 0 ? L - 1 : y - 1, zm = z == 0 ? L - 1 : z - 1;
-        nb[kSelf] = NbrCell{cell, lcell};
-        nb[kMx] = at(xm, y, z);
-        nb[kMy] = at(x, ym, z);
-        nb[kMz] = at(x, y, zm);
-        nb[kMyMz] = at(x, ym, zm);
-        nb[kMxMz] = at(xm, y, zm);
-        nb[kMxMy] = at(xm, ym, z);
+        const bool ix = lx > 0 || d.ntx == 1, iy = ly > 0 || d.nty == 1, iz = lz > 0 || d.ntz == 1;
+        const int sx = lx > 0 ? -1 : min(TX, L) - 1, sy = ly > 0 ? -TX : (min(TY, L) - 1) * TX,
+                  sz = lz > 0 ? -TX * TY : (min(TZ, L) - 1) * (TX * TY);
+        lc[kSelf] = lcell;
+        lc[kMx] = ix ? lcell + sx : -1;
+        lc[kMy] = iy ? lcell + sy : -1;
+        lc[kMz] = iz ? lcell + sz : -1;
+        lc[kMyMz] = iy && iz ? lcell + sy + sz : -1;
+        lc[kMxMz] = ix && iz ? lcell + sx + sz : -1;
+        lc[kMxMy] = ix && iy ? lcell + sx + sy : -1;
+    }
+    // Global indices of those cells (periodic wrap), the cell itself at (x, y, z).
+    __device__ __forceinline__ void global_neighbours(int x, int y, int z, int cell, int (&gc)[kNCellCodes]) const
+    {
+        const int sx = x == 0 ? L - 1 : -1, sy = y == 0 ? L * (L - 1) : -L, sz = z == 0 ? L * L * (L - 1) : -L * L;
+        gc[kSelf] = cell;
+        gc[kMx] = cell + sx;
+        gc[kMy] = cell + sy;
+        gc[kMz] = cell + sz;
+        gc[kMyMz] = cell + sy + sz;
+        gc[kMxMz] = cell + sx + sz;
+        gc[kMxMy] = cell + sx + sy;
     }
 };
 
@@ -262,6 +257,16 @@ __device__ __forceinline__ int lab_load(const int32_t *lab, int x)
 __device__ __forceinline__ void lab_store(int32_t *lab, int x, int v)
 {
     __hip_atomic_store(lab + x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// The same store written through to memory, where the compare-and-swaps of
+// other compute units act: an entry left dirty in this XCD's L2 beside entries
+// they swap costs more than the store saves (unite pass over five L = 128
+// lattices: 476 us with compare-and-swaps only, 527 with plain stores for the
+// lone roots, 441 with these; one lattice 108, 104 and 84).
+__device__ __forceinline__ void lab_store_through(int32_t *lab, int x, int v)
+{
+    __hip_atomic_store(lab + x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Root of local root x in the forest while hooking runs (shortcuts store
@@ -554,45 +559,54 @@ __device__ __forceinline__ void settle_tile_roots(const RepDesc &d, const RepSta
     __syncthreads();
 }
 
-// Site `site` of the neighbour cell `code` (lattice.hpp codes) of the cell
-// at (x, y, z); xm, ym, zm are the wrapped lower coordinates.  Bit 0/1/2 of
-// the 3-bit field of a code says whether the neighbour is one cell lower in
-// x/y/z.
-__device__ __forceinline__ int nbr_site(int code, int site, int x, int y, int z, int xm, int ym, int zm, int L)
-{
-    constexpr uint32_t kLowerAxes = 0u | 1u << 3 | 2u << 6 | 4u << 9 | 6u << 12 | 5u << 15 | 3u << 18;
-    const uint32_t mk = (kLowerAxes >> (3 * code)) & 7u;
-    const int cx = (mk & 1u) ? xm : x, cy = (mk & 2u) ? ym : y, cz = (mk & 4u) ? zm : z;
-    return 16 * cell_index(cx, cy, cz, L) + site;
-}
+// Names and keys of local roots in the merge.  A key is the root's site index
+// with kLone set when the root is a component of one site: every bond it has
+// left is of one tile-crossing tetrahedron, so every hook of it is made by the
+// one workgroup that lists that tetrahedron's pairs and needs no
+// compare-and-swap.  A tile's crossing list names the roots of its own sites
+// by kHere | key, and a site of another tile by the index, in the list array,
+// of the word where that tile keeps the site's key (its port words).
+constexpr int kLone = 1 << 30;
+constexpr int kHere = INT32_MIN;
 
-// Local root of site e (a plain, possibly stale load is exact: the entry of
-// an ordinary site does not change during the global phase, and any value a
-// local root's entry takes decodes to the root itself).
-__device__ __forceinline__ int endpoint_root(const int32_t *lab, int e)
-{
-    const int v = lab[e];
-    return (v < 0 || (v & kTag) || v == e) ? e : v;
-}
-
-// Local root named by a crossing-list entry: a tagged name is a local root
-// already; a site index is looked up (endpoint_root).
-__device__ __forceinline__ int name_root(const int32_t *lab, int name)
-{
-    return (name & kTag) ? (name & kIdxMask) : endpoint_root(lab, name);
-}
+// Port words: after a tile's crossing list (at the end of its stride), the
+// keys of its sites that other tiles' crossing tetrahedra can reach, four per
+// cell of each high face: (x: sites 14, 11, 10, 15), (y: 13, 7, 5, 15), (z: 9,
+// 6, 5, 10), cells in the order of the face's (y, z), (x, z), (x, y).  Along a
+// ragged axis a tile's last cell in the lattice stands for all beyond it, so
+// that a neighbour finds the high face where a full tile has it.  The words
+// are contiguous, where the labels they stand for are scattered over
+// the tile's 32 KB.
+template <int TX, int TY, int TZ>
+struct Ports {
+    static constexpr int kY = 4 * TY * TZ, kZ = kY + 4 * TX * TZ, kWords = kZ + 4 * TX * TY;
+    static constexpr uint32_t kSites[3] = {0xFABEu, 0xF57Du, 0xA569u};  // site of word 4 i + k: nibble k
+    // Word of a site at local cell (x, y, z) on the high face `face`.
+    static constexpr int word(int face, int site, int x, int y, int z)
+    {
+        int k = 0;
+        while (((kSites[face] >> (4 * k)) & 15u) != (uint32_t)site) ++k;
+        return face == 0 ? 4 * (z * TY + y) + k : (face == 1 ? kY + 4 * (z * TX + x) + k : kZ + 4 * (y * TX + x) + k);
+    }
+};
 
 // Crossing-pair emission items of a tile shape: one per (low-face cell c,
 // down tetrahedron f) whose tetrahedron can have a vertex outside the tile
 // (f = 0 on every low face, f = 1/2/3 on the face x/y/z = 0), packed as
-// 4 c + f and sorted by f, so the lanes of a wave mostly share f.  Whether a
-// vertex is outside is decided at run time (an axis with a single tile
-// wraps onto itself).
+// 4 c + f and sorted by f, so the lanes of a wave mostly share f.  port[mu-1]
+// of a vertex mu beyond a low face: which axes it crosses (bits x, y, z of the
+// top four) and its port word in the tile there, 0 when it never leaves.
+// Whether that tile is another one is decided at run time (an axis with a
+// single tile wraps onto itself).
+struct EmitItem {
+    uint16_t item, port[3];
+};
 template <int TX, int TY, int TZ>
 struct EmitItems {
-    uint16_t v[4 * TX * TY * TZ];
+    alignas(8) EmitItem v[4 * TX * TY * TZ];
     int n;
 };
+constexpr uint32_t kLowerAxes = 0u | 1u << 3 | 2u << 6 | 4u << 9 | 6u << 12 | 5u << 15 | 3u << 18;  // axes lowered, per cell code
 template <int TX, int TY, int TZ>
 __host__ __device__ constexpr EmitItems<TX, TY, TZ> make_emit_items()
 {
@@ -600,9 +614,22 @@ __host__ __device__ constexpr EmitItems<TX, TY, TZ> make_emit_items()
     t.n = 0;
     for (int f = 0; f < 4; ++f)
         for (int c = 0; c < TX * TY * TZ; ++c) {
-            const bool fx = c % TX == 0, fy = (c / TX) % TY == 0, fz = c / (TX * TY) == 0;
-            const bool use = f == 0 ? (fx || fy || fz) : (f == 1 ? fx : (f == 2 ? fy : fz));
-            if (use) t.v[t.n++] = (uint16_t)(4 * c + f);
+            const int x = c % TX, y = (c / TX) % TY, z = c / (TX * TY);
+            const bool use = f == 0 ? (x == 0 || y == 0 || z == 0) : (f == 1 ? x == 0 : (f == 2 ? y == 0 : z == 0));
+            if (!use) continue;
+            EmitItem e{};
+            e.item = (uint16_t)(4 * c + f);
+            for (int mu = 1; mu < 4; ++mu) {
+                const SiteRef R = down_vertex(f, mu);
+                const uint32_t low = (kLowerAxes >> (3 * R.cell)) & 7u;
+                const uint32_t out = low & ((x == 0 ? 1u : 0u) | (y == 0 ? 2u : 0u) | (z == 0 ? 4u : 0u));
+                if (!out) continue;
+                const int vx = (low & 1u) ? (x + TX - 1) % TX : x, vy = (low & 2u) ? (y + TY - 1) % TY : y,
+                          vz = (low & 4u) ? (z + TZ - 1) % TZ : z;
+                const int face = (out & 4u) ? 2 : ((out & 2u) ? 1 : 0);
+                e.port[mu - 1] = (uint16_t)(out << 12 | (uint32_t)Ports<TX, TY, TZ>::word(face, R.site, vx, vy, vz));
+            }
+            t.v[t.n++] = e;
         }
     return t;
 }
@@ -644,17 +671,17 @@ constexpr int kUnionWords = 2 * NC;
 // Every site is a vertex of exactly one down tetrahedron, owned by one cell,
 // so the crossing bonds of different cells never join the same pair of
 // sites.  For each down tetrahedron with a vertex outside the tile, each
-// vertex is named by its tile-local root with the tag bit set (inside) or
-// by its site index (outside), and per component of the tetrahedron's
-// active bonds the edges from the component's smallest vertex to the others
-// whose name differs are emitted: at most 3 pairs per tetrahedron, none
-// repeated.  These tetrahedra belong to the cells of the low faces; they
-// are handed out to all threads as a table of (cell, tetrahedron) items.
+// vertex is named by its tile-local root (inside) or by its port word
+// (outside), and per component of the tetrahedron's active bonds the edges
+// from the component's first vertex to the others whose name differs are
+// emitted: at most 3 pairs per tetrahedron, none repeated.  These tetrahedra
+// belong to the cells of the low faces; they are handed out to all threads as
+// a table of (cell, tetrahedron) items.
 template <int TX, int TY, int TZ>
 __device__ __forceinline__ void tile_components(const RepDesc &d, const TileIdx<TX, TY, TZ> &ti, int tile, int tid,
                                                 int lcid, bool valid, int cell, uint64_t act,
                                                 const int (&lc)[kNCellCodes], uint32_t *P, uint32_t *U,
-                                                const uint8_t *K4)
+                                                const uint8_t *K4, uint32_t *NB /* 8 words */)
 {
     constexpr int NC = TX * TY * TZ;
     static_assert(NC % 64 == 0, "tiles are whole waves");
@@ -742,7 +769,25 @@ __device__ __forceinline__ void tile_components(const RepDesc &d, const TileIdx<
     U[lcid] = (uint32_t)(16 * cell - 17 * lcid);
     uint32_t *DA = U + NC;  // active bonds of the cells' down tetrahedra
     DA[lcid] = (uint32_t)(act >> 24);
+    // Sites without an active bond in their up tetrahedron: bit 6 f + mu, in
+    // the cell's unused 17th forest word.
+    const uint32_t ub = (uint32_t)act & 0xFFFFFFu;
+    const uint32_t bare = (~(ub | ub >> 1 | ub >> 2) & 0x41041u) | (~(ub | ub >> 3 | ub >> 4) & 0x41041u) << 1 |
+                          (~(ub >> 1 | ub >> 3 | ub >> 5) & 0x41041u) << 2 | (~(ub >> 2 | ub >> 4 | ub >> 5) & 0x41041u) << 3;
+    node(P, base + 64) = bare;
+    // Port words of the tiles one step down the axes in the bits of q (q = 0:
+    // this tile's own).
+    using PT = Ports<TX, TY, TZ>;
+    const int own = (tile + 1) * d.list_stride - PT::kWords;
+    if (tid < 8) {
+        const int qx = (tid & 1) ? (ti.bx == 0 ? d.ntx - 1 : ti.bx - 1) : ti.bx;
+        const int qy = (tid & 2) ? (ti.by == 0 ? d.nty - 1 : ti.by - 1) : ti.by;
+        const int qz = (tid & 4) ? (ti.bz == 0 ? d.ntz - 1 : ti.bz - 1) : ti.bz;
+        NB[tid] = (uint32_t)(((qz * d.nty + qy) * d.ntx + qx + 1) * d.list_stride - PT::kWords);
+    }
     __syncthreads();
+    const int L = d.L;
+    const int ex = min(TX, L - ti.bx * TX) - 1, ey = min(TY, L - ti.by * TY) - 1, ez = min(TZ, L - ti.bz * TZ) - 1;
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         // cell of the root's slot: offset / 68 (unsigned: past 2^31 for 16x8x8 tiles, below 2^32)
@@ -755,16 +800,50 @@ __device__ __forceinline__ void tile_components(const RepDesc &d, const TileIdx<
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             out[q] = make_int4((int)r[4 * q], (int)r[4 * q + 1], (int)r[4 * q + 2], (int)r[4 * q + 3]);
+        // Port words.  The tetrahedron that reaches such a site from another
+        // tile has united nothing here, so a bare one is a component of one
+        // site.  Along a ragged axis the last cell also stands at the tile's
+        // full edge, where a neighbour across that axis looks for it.
+        auto key4 = [&](int a, int b, int c4, int e) {
+            auto key = [&](int k) { return (int)(r[k] | __builtin_amdgcn_ubfe(bare, 6u * (k / 4) + k % 4, 1u) << 30); };
+            return make_int4(key(a), key(b), key(c4), key(e));
+        };
+        int4 *pw = reinterpret_cast<int4 *>(d.pairs + own);
+        const int lx = lcid % TX, ly = (lcid / TX) % TY, lz = lcid / (TX * TY);
+        const bool full = ex == TX - 1 && ey == TY - 1 && ez == TZ - 1;
+        const int vx = lx == ex ? TX - 1 : lx, vy = ly == ey ? TY - 1 : ly, vz = lz == ez ? TZ - 1 : lz;
+        if (lx == ex) {
+            const int4 w = key4(14, 11, 10, 15);
+            pw[lz * TY + ly] = w;
+            if (!full) {
+                pw[lz * TY + vy] = w;
+                pw[vz * TY + ly] = w;
+            }
+        }
+        if (ly == ey) {
+            const int4 w = key4(13, 7, 5, 15);
+            pw[PT::kY / 4 + lz * TX + lx] = w;
+            if (!full) {
+                pw[PT::kY / 4 + lz * TX + vx] = w;
+                pw[PT::kY / 4 + vz * TX + lx] = w;
+            }
+        }
+        if (lz == ez) {
+            const int4 w = key4(9, 6, 5, 10);
+            pw[PT::kZ / 4 + ly * TX + lx] = w;
+            if (!full) {
+                pw[PT::kZ / 4 + ly * TX + vx] = w;
+                pw[PT::kZ / 4 + vy * TX + lx] = w;
+            }
+        }
     }
     __syncthreads();
     // Crossing pairs, one item (cell, down tetrahedron) per thread and round.
     // Each round places its pairs in item order: a lane's offset is the
     // number of pairs of the lanes below it (two ballots of the 0..3 pair
-    // count), plus the totals of the lower waves, kept in U (free by now).
-    const int L = d.L;
+    // count), plus the totals of the lower waves, kept in U.
     int2 *list = reinterpret_cast<int2 *>(d.pairs + (int64_t)tile * d.list_stride) + 1;
     constexpr uint64_t kVert0 = down_vertex_bytes(0), kVert1 = down_vertex_bytes(1);
-    constexpr uint32_t kLowerAxes = 0u | 1u << 3 | 2u << 6 | 4u << 9 | 6u << 12 | 5u << 15 | 3u << 18;
     constexpr int kItems = make_emit_items<TX, TY, TZ>().n;
     int placed = 0;  // pairs listed so far (the same in every thread)
     for (int jb = 0; jb < kItems; jb += NC) {
@@ -772,31 +851,43 @@ __device__ __forceinline__ void tile_components(const RepDesc &d, const TileIdx<
         int2 q[3];
         bool e[3] = {false, false, false};
         if (j < kItems) {
-            const int item = kEmitItems<TX, TY, TZ>.v[j];
-            const int c = item >> 2, f = item & 3;
+            const EmitItem it = kEmitItems<TX, TY, TZ>.v[j];
+            const int c = it.item >> 2, f = it.item & 3;
             const int ix = c % TX, iy = (c / TX) % TY, iz = c / (TX * TY);
-            const int cx = ti.bx * TX + ix, cy = ti.by * TY + iy, cz = ti.bz * TZ + iz;
-            if (cx < L && cy < L && cz < L) {
-                const int xm = cx == 0 ? L - 1 : cx - 1, ym = cy == 0 ? L - 1 : cy - 1, zm = cz == 0 ? L - 1 : cz - 1;
+            if (ix <= ex && iy <= ey && iz <= ez) {
+                const uint32_t code = K4[(DA[c] >> (6 * f)) & 63u];
                 const uint64_t vb = (f < 2) ? kVert0 : kVert1;
-                bool outside = false;
+                bool outside = false, alone[4];
                 int id[4];
 #pragma unroll
                 for (int mu = 0; mu < 4; ++mu) {
                     const uint32_t v = (uint32_t)(vb >> (8 * (4 * (f & 1) + mu))) & 0xFFu;
-                    const int code = (int)(v >> 4), site = (int)(v & 15u);
-                    const uint32_t mk = (kLowerAxes >> (3 * code)) & 7u;
-                    const int nx = (mk & 1u) ? xm : cx, ny = (mk & 2u) ? ym : cy, nz = (mk & 4u) ? zm : cz;
-                    const NbrCell nb = ti.at(nx, ny, nz);
-                    if (nb.lcell >= 0) {
-                        id[mu] = (int)node(P, node_off(16 * nb.lcell + site)) | kTag;
+                    const uint32_t low = (kLowerAxes >> (3 * (v >> 4))) & 7u;
+                    const uint32_t port = mu == 0 ? 0u : it.port[mu == 0 ? 0 : mu - 1];
+                    const int b = (int)NB[port >> 12];
+                    if (b == own) {
+                        // in the tile; an axis of one tile wraps onto itself
+                        const int x = (low & 1u) ? (ix == 0 ? ex : ix - 1) : ix;
+                        const int y = (low & 2u) ? (iy == 0 ? ey : iy - 1) : iy;
+                        const int z = (low & 4u) ? (iz == 0 ? ez : iz - 1) : iz;
+                        const uint32_t off = 68u * (uint32_t)((z * TY + y) * TX + x), k = v & 15u;
+                        id[mu] = kHere | (int)node(P, off + 4u * k);
+                        alone[mu] = (node(P, off + 64u) >> (6u * (k >> 2) + (k & 3u))) & 1u;
                     } else {
-                        id[mu] = 16 * nb.gcell + site;
+                        id[mu] = b + (int)(port & 0xFFFu);
+                        alone[mu] = false;
                         outside = true;
                     }
                 }
                 if (outside) {
-                    const uint32_t code = K4[(DA[c] >> (6 * f)) & 63u];
+                    // a bare site here is a component of its own unless this
+                    // tetrahedron joined it to another site of the tile
+                    const bool e01 = id[0] == id[1], e02 = id[0] == id[2], e03 = id[0] == id[3], e12 = id[1] == id[2],
+                               e13 = id[1] == id[3], e23 = id[2] == id[3];
+                    id[0] |= alone[0] && !(e01 || e02 || e03) ? kLone : 0;
+                    id[1] |= alone[1] && !(e01 || e12 || e13) ? kLone : 0;
+                    id[2] |= alone[2] && !(e02 || e12 || e23) ? kLone : 0;
+                    id[3] |= alone[3] && !(e03 || e13 || e23) ? kLone : 0;
 #pragma unroll
                     for (int mu = 1; mu < 4; ++mu) {
                         const int rp = (code >> (2 * mu)) & 3;
@@ -811,8 +902,7 @@ __device__ __forceinline__ void tile_components(const RepDesc &d, const TileIdx<
         const uint64_t b0 = __ballot(npair & 1u), b1 = __ballot(npair & 2u);
         const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(b0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b0, 0u)) +
                                2u * __builtin_amdgcn_mbcnt_hi((uint32_t)(b1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b1, 0u));
-        const int wave = tid >> 6;
-        if ((tid & 63) == 0) U[wave] = (uint32_t)(__popcll(b0) + 2 * __popcll(b1));
+        if (lane == 0) U[wave] = (uint32_t)(__popcll(b0) + 2 * __popcll(b1));
         __syncthreads();
         int at = placed + (int)below, total = 0;
         for (int w = 0; w < NC / 64; ++w) {
@@ -877,17 +967,25 @@ struct UniteLds {
     int HK[kTileRoots];           // local root of the slot, -1 if free
     int HP[kTileRoots];           // LDS parent slot
     uint64_t BEST[kTileRoots];    // per group: smallest member << 10 | its slot
-    int16_t PA[kMaxListed], PB[kMaxListed];
-    int nroots, missed;
+    int16_t PA[kMaxListed];
+    alignas(8) int16_t PB[kMaxListed];
+    int nroots, missed, direct, nlost;
 };
 
 template <int NT, bool COUNT = false>
-__device__ __forceinline__ void unite_tile_pairs(int32_t *lab, int *head, int n, int list_stride, int tid, UniteLds &S,
+__device__ __forceinline__ void unite_tile_pairs(int32_t *lab, int *head, int64_t tile_words, int list_stride, int tid, UniteLds &S,
                                                  unsigned long long *counts, bool keep_roots)
 {
     constexpr int H = kTileRoots;                    // root slots
     constexpr int kMaxListed = UniteLds::kMaxListed;  // pairs kept in LDS
     const int2 *list = reinterpret_cast<const int2 *>(head) + 1;
+    // The thread's first pairs are fetched along with their number (any words
+    // of the tile's stride will do), one memory latency earlier.
+    constexpr int kBatch = 4;
+    const int n = head[0], room = (list_stride - 2) / 2;
+    int2 first[kBatch];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) first[i] = list[min(tid + i * NT, room - 1)];
     for (int k = tid; k < H; k += NT) {
         S.HK[k] = -1;
         S.HP[k] = k;
@@ -896,8 +994,12 @@ __device__ __forceinline__ void unite_tile_pairs(int32_t *lab, int *head, int n,
     if (tid == 0) {
         S.nroots = 0;
         S.missed = 0;
+        S.direct = 0;
+        S.nlost = 0;
     }
     __syncthreads();
+    const int *words = head - (int64_t)tile_words;  // start of the list array, which port names index
+    auto name_key = [&](int name) { return name < 0 ? (name & INT32_MAX) : words[name]; };
     auto insert = [&](int key) {
         uint32_t h = (uint32_t)key * 0x9E3779B1u;
         h ^= h >> 15;
@@ -910,16 +1012,15 @@ __device__ __forceinline__ void unite_tile_pairs(int32_t *lab, int *head, int n,
         return -1;
     };
     // Four of the thread's pairs at a time: their names are resolved with all
-    // label loads in flight together, then entered in the table.
-    constexpr int kBatch = 4;
+    // port words in flight together, then entered in the table.
     for (int k0 = tid; k0 < n; k0 += kBatch * NT) {
         int ra[kBatch], rb[kBatch];
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
             const int k = k0 + i * NT;
-            const int2 p = k < n ? list[k] : make_int2(kTag, kTag);
-            ra[i] = name_root(lab, p.x);
-            rb[i] = name_root(lab, p.y);
+            const int2 p = k >= n ? make_int2(kHere, kHere) : (k0 == tid ? first[i] : list[k]);
+            ra[i] = name_key(p.x);
+            rb[i] = name_key(p.y);
         }
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
@@ -927,7 +1028,10 @@ __device__ __forceinline__ void unite_tile_pairs(int32_t *lab, int *head, int n,
             if (k >= n) break;
             const int sa = ra[i] == rb[i] ? -1 : insert(ra[i]), sb = ra[i] == rb[i] ? -1 : insert(rb[i]);
             const bool listed = k < kMaxListed && sa >= 0 && sb >= 0;
-            if (!listed && ra[i] != rb[i]) forest_unite<COUNT>(lab, ra[i], rb[i], counts);
+            if (!listed && ra[i] != rb[i]) {
+                forest_unite<COUNT>(lab, ra[i] & kIdxMask, rb[i] & kIdxMask, counts);
+                S.direct = 1;
+            }
             if (ra[i] != rb[i] && (sa < 0 || sb < 0)) S.missed = 1;
             if (k < kMaxListed) {
                 S.PA[k] = (int16_t)(listed ? sa : -1);
@@ -967,7 +1071,7 @@ __device__ __forceinline__ void unite_tile_pairs(int32_t *lab, int *head, int n,
     __syncthreads();
     for (int s = tid; s < H; s += NT) {
         if (S.HK[s] < 0) continue;
-        atomicMin(&S.BEST[slot_find(s)], (uint64_t)S.HK[s] << 10 | (uint64_t)s);
+        atomicMin(&S.BEST[slot_find(s)], (uint64_t)(S.HK[s] & kIdxMask) << 10 | (uint64_t)s);
     }
     __syncthreads();
     // The pairs are read: overwrite them with the distinct local roots (at
@@ -979,16 +1083,25 @@ __device__ __forceinline__ void unite_tile_pairs(int32_t *lab, int *head, int n,
             if (S.HK[s] < 0) continue;
             const int j = atomicAdd(&S.nroots, 1);
             S.PA[s] = (int16_t)j;
-            head[2 + j] = S.HK[s];
+            head[2 + j] = S.HK[s] & kIdxMask;
         }
     }
     __syncthreads();
     // Each member of a group other than its smallest is hooked under the
-    // smallest (a smaller node, so a valid parent for a root).  A member that
-    // is still a root of the global forest is hooked by one compare-and-swap,
-    // without a walk, and the thread's compare-and-swaps are in flight
-    // together; one that finds the member already hooked continues the union
-    // from the parent it returned.
+    // smallest (a smaller node, so a valid parent for a root).  A lone root is
+    // hooked by no other workgroup, and nothing hangs below one that is not its
+    // group's smallest: a plain store does (unless a pair beyond the LDS tables
+    // was united directly).  These are 44% of the hooks at T_c, and the pass is
+    // bound by the rate of the rest: another member that is still a root of
+    // the global forest is hooked by one compare-and-swap, without a walk, and
+    // the thread's compare-and-swaps are in flight together; one that finds
+    // the member already hooked is lost, and its union continues from the
+    // parent it returned.
+    const bool plain = !S.direct;
+    // Lost ones (the parent found, the group's smallest member) are shared out
+    // over the threads in the space of the listed pairs' second slots.
+    int2 *lost = reinterpret_cast<int2 *>(S.PB);
+    constexpr int kMaxLost = (int)(sizeof(S.PB) / sizeof(int2));
     constexpr int kSlotsPerThread = (H + NT - 1) / NT;
     constexpr int kHookBatch = kSlotsPerThread < 4 ? kSlotsPerThread : 4;
     for (int i0 = 0; i0 < kSlotsPerThread; i0 += kHookBatch) {
@@ -1002,8 +1115,10 @@ __device__ __forceinline__ void unite_tile_pairs(int32_t *lab, int *head, int n,
                 const int rs = (int)(S.BEST[slot_find(s)] & (uint64_t)(H - 1));
                 if (!S.missed && with_reps) head[2 + H + S.PA[s]] = S.PA[rs];
                 if (rs != s) {
-                    ha[i] = S.HK[s];
-                    hb[i] = S.HK[rs];
+                    const int key = S.HK[s];
+                    hb[i] = S.HK[rs] & kIdxMask;
+                    if (plain && (key & kLone)) lab_store_through(lab, key & kIdxMask, kTag | hb[i]);
+                    else ha[i] = key & kIdxMask;
                 }
             }
         }
@@ -1016,9 +1131,15 @@ __device__ __forceinline__ void unite_tile_pairs(int32_t *lab, int *head, int n,
                 atomicAdd(&counts[0], 1ull);
                 if (old[i] == ha[i]) atomicAdd(&counts[1], 1ull);
             }
-            if (old[i] != ha[i]) forest_unite<COUNT>(lab, old[i] & kIdxMask, hb[i], counts);
+            if (old[i] == ha[i]) continue;
+            const int j = atomicAdd(&S.nlost, 1);
+            if (j < kMaxLost) lost[j] = make_int2(old[i] & kIdxMask, hb[i]);
+            else forest_unite<COUNT>(lab, old[i] & kIdxMask, hb[i], counts);
         }
     }
+    __syncthreads();
+    const int nlost = min(S.nlost, kMaxLost);
+    for (int j = tid; j < nlost; j += NT) forest_unite<COUNT>(lab, lost[j].x, lost[j].y, counts);
     if (tid == 0 && keep_roots) head[1] = S.missed ? 0 : (with_reps ? -S.nroots : S.nroots);
 }
 
@@ -1074,7 +1195,8 @@ __device__ __forceinline__ void store_tile(const RepDesc &d, const RepState &st,
     };
     for (int k = tid; k < 2 * n; k += NT) {
         const int2 p = list[k >> 1];
-        add(name_root(lab, (k & 1) ? p.y : p.x));
+        const int name = (k & 1) ? p.y : p.x;
+        add((name < 0 ? name : d.pairs[name]) & kIdxMask);
     }
     __syncthreads();
     for (int k = tid; k < H; k += NT) {
@@ -1088,23 +1210,105 @@ template <int NT, bool COUNT = false>
 __device__ __forceinline__ void unite_tile(const RepDesc &d, int tile, int tid, UniteLds &S,
                                            unsigned long long *counts = nullptr, bool keep_roots = true)
 {
-    int *head = d.pairs + (int64_t)tile * d.list_stride;
-    unite_tile_pairs<NT, COUNT>(d.label, head, head[0], d.list_stride, tid, S, counts, keep_roots);
+    const int64_t at = (int64_t)tile * d.list_stride;
+    int *head = d.pairs + at;
+    unite_tile_pairs<NT, COUNT>(d.label, head, at, d.list_stride, tid, S, counts, keep_roots);
 }
 
-// The unite pass of a chain.  COUNT: it counts its compare-and-swaps into
-// c.counts (measurement runs).  The chains settle their roots in the flip
-// pass and run no store pass, so the lists are left as they are.
+// ------------------------------------------------------------- records ---
+// The record of the last sweep (ring slot st.e_pending, sweep st.t - 1): its
+// magnetisation from the ntiles partials of that sweep's settle-and-flip pass, its
+// energy from the partials at e_at (the next tile pass, whose tiles count the
+// energy of the state entering the sweep, or the energy tail), in an order
+// fixed by the block size.  with_energy = false leaves the energy to a later
+// call.  A block of kBlock threads; red: 16 words of 8 bytes per sum.
+template <int NV>
+__device__ __forceinline__ void write_pending_record(const RepDesc &d, const RepState &st, int ntiles, int tid,
+                                                     bool with_energy, int e_at, int e_n, void *red)
+{
+    DevRecord r;
+    r.sweep = (int64_t)st.t - 1;
+    r.bond_sum = 0;
+    r.M_int = 0;
+    r.reserved = 0;
+    r.E = 0.0;
+    r.M[0] = r.M[1] = r.M[2] = 0.0;
+    double m;
+    if constexpr (NV == 1) {
+        int64_t v[2] = {0, 0};  // magnetisation, bond sum
+        for (int k = tid; k < ntiles; k += kBlock) v[0] += d.ipart[d.mpart_off + k];
+        if (with_energy)
+            for (int k = tid; k < e_n; k += kBlock) v[1] += d.ipart[e_at + k];
+        block_sum_n<int64_t, 2>(v, (int64_t *)red);
+        r.bond_sum = v[1];
+        r.M_int = v[0];
+        if (with_energy) r.E = -d.J * (double)v[1];
+        r.M[0] = (double)v[0];
+        m = (double)v[0] / (double)d.N;
+    } else {
+        double v[NV + 1];
+#pragma unroll
+        for (int q = 0; q <= NV; ++q) v[q] = 0.0;
+        for (int k = tid; k < ntiles; k += kBlock)
+#pragma unroll
+            for (int q = 0; q < NV; ++q) v[q] += d.dpart[d.mpart_off * (1 + q) + k];
+        if (with_energy)
+            for (int k = tid; k < e_n; k += kBlock) v[NV] += d.dpart[e_at + k];
+        block_sum_n<double, NV + 1>(v, (double *)red);
+        if (with_energy) r.E = -d.J * v[NV];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) r.M[q] = v[q];
+        m = sqrt(r.M[0] * r.M[0] + r.M[1] * r.M[1] + r.M[2] * r.M[2]) / (double)d.N;
+    }
+    r.m2 = m * m;
+    r.m4 = r.m2 * r.m2;
+    if (tid == 0) d.ring[st.e_pending] = r;
+}
+
+__device__ __forceinline__ void write_pending_record(const RepDesc &d, int model, const RepState &st, int ntiles, int tid,
+                                                     bool with_energy, int e_at, int e_n, void *red)
+{
+    if (model == 1) write_pending_record<1>(d, st, ntiles, tid, with_energy, e_at, e_n, red);
+    else if (model == 2) write_pending_record<2>(d, st, ntiles, tid, with_energy, e_at, e_n, red);
+    else write_pending_record<3>(d, st, ntiles, tid, with_energy, e_at, e_n, red);
+}
+
+// The unite pass of a chain: one workgroup per tile, and one per replica (the
+// last of the grid) that writes the record of the previous sweep, whose sums
+// are complete by now, and the state for the settle-and-flip pass.  A kernel
+// of its own for the records, one workgroup per replica, had cost 4 to 5 us
+// and a launch gap per sweep, 5% to 9% of a sweep of L <= 64.  COUNT: it
+// counts its compare-and-swaps into c.counts (measurement runs).  The chains
+// settle their roots in the flip pass and run no store pass, so the lists are
+// left as they are.
 template <bool COUNT = false>
 __global__ __launch_bounds__(kUniteThreads) void k_forest(Chain c)
 {
+    static_assert(kUniteThreads == kBlock, "the record block");
     __shared__ UniteLds S;
-    const int blk = xcd_block(blockIdx.x, gridDim.x);
+    if ((int)blockIdx.x >= c.ntile_blocks) {
+        const int rep = (int)blockIdx.x - c.ntile_blocks;
+        const RepDesc &d = c.desc[rep];
+        const RepState st = c.state[rep][0];
+        if (threadIdx.x == 0) c.state[rep][1] = st;
+        if (st.remaining > 0 && st.e_pending >= 0)
+            write_pending_record(d, c.model, st, mag_partials(c.state[rep]), threadIdx.x, true, 0, d.ntx * d.nty * d.ntz,
+                                 S.BEST);
+        return;
+    }
+    const int blk = xcd_block(blockIdx.x, c.ntile_blocks);
     const int rep = c.tile_rep[blk];
-    const RepState st = *c.state[rep];
-    if (st.remaining <= 0) return;
+    if (c.state[rep]->remaining <= 0) return;
     const RepDesc &d = c.desc[rep];
     unite_tile<kUniteThreads, COUNT>(d, blk - d.tile_base, threadIdx.x, S, c.counts, false);
+}
+
+// First block of a replica in the settle-and-flip pass: the state of the next
+// sweep and the number of magnetisation partials this pass leaves.
+__device__ __forceinline__ void advance_state(RepState *s, const RepState &st, const RepDesc &d)
+{
+    s[0] = advanced(st, d.ring_cap);
+    mag_partials(s) = d.ntx * d.nty * d.ntz;
 }
 
 // Shape dispatch: calls F::template run<TX, TY, TZ>(args...).
@@ -1120,8 +1324,9 @@ hipError_t with_tile_shape(int shape, Args &&...args)
     }
 }
 
-// Launcher of the model-independent unite pass (tile_common.hip).
+// Launchers of the model-independent passes (tile_common.hip).
 hipError_t launch_unite(const Chain &c, hipStream_t st, const LaunchHook &hook);
+hipError_t launch_pending_records(const Chain &c, bool with_energy, hipStream_t st, const LaunchHook &hook);
 
 // Per-model chain launchers (ising_tiled.hip, on_tiled.hip).
 hipError_t launch_ising_sweep(const Chain &c, hipStream_t st, const LaunchHook &hook);
