@@ -212,7 +212,7 @@ int pyro_sw_kernel_times(pyro_sw *h, const char **names, int64_t *launches, doub
  *                          stream on every call, so that the latency-bound
  *                          passes of one slice overlap the arithmetic of
  *                          another (members are dealt largest first to the
- *                          lightest slice; default min(n, 8)).  Changes speed
+ *                          lightest slice; default min(n, 2)).  Changes speed
  *                          only, never results.
  *   pyro_sw_group_set_mode how the Ising members are swept (the O(n)
  *                          members always use per-sweep graphs):

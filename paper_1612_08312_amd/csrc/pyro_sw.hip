@@ -109,6 +109,13 @@ int default_tile_shape(int L) { return L >= 96 ? kTile888 : (L >= 48 ? kTile884 
 
 constexpr int kRing = 16384;  // device records per lattice before a forced drain
 constexpr int kMaxSlices = 8;  // concurrent slices of a group
+// Slices of a new group.  Two streams let one slice's merge, bound by memory
+// latency and atomics, run beside the other's arithmetic; more only cut the
+// launches smaller, and past four they share hardware queues.  Per sweep with
+// 1 / 2 / 4 / 8 slices: five L = 128 lattices (five at most) 1.33 / 1.33 /
+// 1.34 / 1.34 ms, 48 Ising replicas of L = 8 to 48 460 / 446 / 486 / 527 us,
+// 27 Heisenberg lattices of L = 24 to 48 633 / 609 / 609 / 599 us.
+constexpr int kDefaultSlices = 2;
 constexpr size_t kAlign = 256;
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -1301,7 +1308,7 @@ int pyro_sw_group_create(pyro_sw_group **out, pyro_sw *const *members, int n, vo
             g->resident = it->second.resident;
         }
     }
-    if (int rc = make_slices(g, std::min(n, kMaxSlices))) {
+    if (int rc = make_slices(g, std::min(n, kDefaultSlices))) {
         pyro_sw_group_destroy(g);
         return rc;
     }
