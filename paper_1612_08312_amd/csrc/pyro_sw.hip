@@ -303,6 +303,7 @@ struct pyro_sw {
     // solo sweeps
     ChainTables solo;
     int solo_shape = kTile888;  // set from L at init (default_tile_shape)
+    bool shape_chosen = false;  // set by the caller: the sweeps are tiled
     hipGraphExec_t solo_exec = nullptr;
     uint64_t param_version = 1, solo_version = 0;
     Timer timer;
@@ -645,6 +646,18 @@ LaunchHook hook_of(Timer &tm, hipStream_t st)
     return tm.mask ? tm.hook() : LaunchHook{nullptr, nullptr, nullptr};
 }
 
+// A lone small pure Ising lattice sweeps LDS-resident, the whole lattice in
+// one workgroup, unless the caller chose a tile shape or times the kernels.
+// Resident against tiled, us per sweep of a long call: L = 4 5.7 / 31, L = 8
+// 11 / 43, L = 12 34 / 53, L = 13 43 / 53.  Setting up costs a call of one
+// sweep more than it gains only beyond L = 12 (L = 13 with its record read:
+// 108 / 106 us).
+bool solo_resident(const pyro_sw *h, int64_t n)
+{
+    return h->model == PYRO_ISING && (h->L <= 12 || (h->L <= kQuadMaxL && n >= 4)) && !h->diluted && !h->shape_chosen &&
+           h->timer.mask == 0;
+}
+
 // Energy of the pending record (tail), then copy the ring to the host queue.
 int drain(pyro_sw *h)
 {
@@ -880,6 +893,15 @@ int pyro_sw_sweep(pyro_sw *h, int64_t n_sweeps)
         if (h->solo_version != h->param_version) HIP_OR_FAIL(&h->broken, build_solo_chain(h));
         RepState armed = h->hs;
         armed.remaining = (int32_t)chunk;
+        if (solo_resident(h, chunk)) {  // every sweep of the chunk in one launch, records complete
+            const LaunchHook none{nullptr, nullptr, nullptr};
+            HIP_OR_FAIL(&h->broken, launch_resident_ising(h->solo.chain, h->L, &armed, h->stream, none));
+            h->hs.t += (uint32_t)chunk;
+            h->hs.ring_used += (int32_t)chunk;
+            h->hs.e_pending = -1;
+            n_sweeps -= chunk;
+            continue;
+        }
         k_arm_one<<<1, 64, 0, h->stream>>>(h->d_state, armed);
         HIP_OR_FAIL(&h->broken, hipGetLastError());
         if (tm.mask) {
@@ -1001,6 +1023,7 @@ int pyro_sw_set_tile_shape(pyro_sw *h, int shape)
     if (rc) return rc;
     if (shape < 0 || shape >= kNumTileShapes) return fail(PYRO_EINVAL, "unknown tile shape");
     h->solo_shape = shape;
+    h->shape_chosen = true;
     h->param_version++;
     return PYRO_OK;
 }
@@ -1379,7 +1402,7 @@ static int group_run(pyro_sw_group *g, int64_t reps)
     if (tm.mask) {  // every kernel in order on the group's stream
         const LaunchHook hook = hook_of(tm, g->stream);
         if (g->res.chain.nreps > 0)
-            HIP_OR_FAIL(&g->broken, launch_resident_ising(g->res.chain, g->res_maxL, g->stream, hook));
+            HIP_OR_FAIL(&g->broken, launch_resident_ising(g->res.chain, g->res_maxL, nullptr, g->stream, hook));
         for (auto &sg : g->subs)
             if (slice_persistent(g, sg))
                 HIP_OR_FAIL(&g->broken, launch_ising_persistent(sg.chains[0].chain, sg.chains[0].d_ctl,
@@ -1410,7 +1433,7 @@ static int group_run(pyro_sw_group *g, int64_t reps)
     }
     if (!g->rexec && g->res.chain.nreps > 0)
         HIP_OR_FAIL(&g->broken, capture_graph(
-                                    [&](hipStream_t cs2) { return launch_resident_ising(g->res.chain, g->res_maxL, cs2, none); },
+                                    [&](hipStream_t cs2) { return launch_resident_ising(g->res.chain, g->res_maxL, nullptr, cs2, none); },
                                     &g->rexec));
     auto run_slice = [&](SubGroup &sg, hipStream_t st) -> int {
         if (sg.pexec) HIP_OR_FAIL(&g->broken, hipGraphLaunch(sg.pexec, st));

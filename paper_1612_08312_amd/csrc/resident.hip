@@ -1,5 +1,5 @@
-// LDS-resident Swendsen-Wang sweeps of small Ising lattices (L <= 16): one
-// workgroup holds a whole lattice in LDS and runs all of its sweeps of a call
+// LDS-resident Swendsen-Wang sweeps of small Ising lattices (L <= 16; up to
+// kQuadMaxL by the quad kernel below): one workgroup holds a whole lattice in LDS and runs all of its sweeps of a call
 // in one launch, with only workgroup barriers between the steps.  The method
 // is the one of the tiled sweep (Sec. 1-2 of the paper: bond activation,
 // cluster labeling, flip of each cluster with probability 1/2, moments of
@@ -32,10 +32,43 @@
 #include "lattice.hpp"
 #include "philox.hpp"
 #include "resident.hpp"
+#include "tile_common.hpp"
 
 namespace pyro {
 
 namespace {
+
+// Record of one sweep from its exact sums (bond sum B, down spins D).
+__device__ __forceinline__ DevRecord ising_record(const RepDesc &d, uint32_t sweep, int64_t B, int64_t D)
+{
+    const int64_t M = d.N - 2 * D;
+    DevRecord rec;
+    rec.sweep = sweep;
+    rec.bond_sum = B;
+    rec.M_int = M;
+    rec.reserved = 0;
+    rec.E = -d.J * (double)B;
+    rec.M[0] = (double)M;
+    rec.M[1] = 0.0;
+    rec.M[2] = 0.0;
+    const double mm = (double)M / (double)d.N;
+    rec.m2 = mm * mm;
+    rec.m4 = rec.m2 * rec.m2;
+    return rec;
+}
+
+// 16 int8 spins of a cell's mask (+1 = 0x01, -1 = 0xFF).
+__device__ __forceinline__ int4 mask_spins(uint32_t m)
+{
+    uint32_t w[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        w[q] = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) w[q] |= (((m >> (4 * q + b)) & 1u) ? 0xFFu : 0x01u) << (8 * b);
+    }
+    return make_int4((int)w[0], (int)w[1], (int)w[2], (int)w[3]);
+}
 
 typedef __attribute__((address_space(3))) volatile uint16_t lds_u16;
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
@@ -98,11 +131,11 @@ __device__ __forceinline__ void unite16(lds_u16 *PF, uint32_t a, uint32_t b)
 // One workgroup of kResidentThreads threads per replica of the chain (all of
 // edge L <= kResidentMaxL, no vacant sites): `remaining` sweeps, records into
 // the ring, then the state is advanced as the tiled finalize would.
-__global__ __launch_bounds__(kResidentThreads) void k_resident_ising(Chain c)
+__global__ __launch_bounds__(kResidentThreads) void k_resident_ising(Chain c, RepState armed, bool use_armed)
 {
     extern __shared__ __align__(16) char lds[];
     const int rep = blockIdx.x;
-    const RepState st = *c.state[rep];
+    const RepState st = use_armed ? armed : *c.state[rep];
     if (st.remaining <= 0) return;
     const RepDesc &d = c.desc[rep];
     const int L = d.L;
@@ -142,6 +175,19 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident_ising(Chain c)
 #define PYRO_DOWN_OF(j, m)                                                                                   \
     down_mask16((m), SMK[nbc[j][kMx]], SMK[nbc[j][kMy]], SMK[nbc[j][kMz]], SMK[nbc[j][kMyMz]],             \
                 SMK[nbc[j][kMxMz]], SMK[nbc[j][kMxMy]])
+    if (st.e_pending >= 0) {  // the record of a tiled sweep before this call: uniform
+        int64_t bsum = 0, down = 0;
+#pragma unroll
+        for (int j = 0; j < kCellsPerThread; ++j) {
+            if (tid + j * NT >= ncell) continue;
+            const uint32_t m = SMK[tid + j * NT];
+            bsum += 2 * (int64_t)__popcll(aligned48(m, PYRO_DOWN_OF(j, m))) - 48;
+            down += __popc(m);
+        }
+        const int64_t B = block_sum<int64_t>(bsum, red);
+        const int64_t D = block_sum<int64_t>(down, red);
+        if (tid == 0) d.ring[st.e_pending] = ising_record(d, st.t - 1, B, D);
+    }
     for (int s = 0; s < st.remaining; ++s) {
         const uint32_t t = st.t + (uint32_t)s;
         // 1. activation; up tetrahedra seed the forest
@@ -232,22 +278,7 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident_ising(Chain c)
         const int64_t D = block_sum<int64_t>(down, red);
         if (tid == 0) {
             const int slot = st.ring_used + s;
-            if (slot < d.ring_cap) {
-                const int64_t M = (int64_t)N - 2 * D;
-                DevRecord rec;
-                rec.sweep = t;
-                rec.bond_sum = B;
-                rec.M_int = M;
-                rec.reserved = 0;
-                rec.E = -d.J * (double)B;
-                rec.M[0] = (double)M;
-                rec.M[1] = 0.0;
-                rec.M[2] = 0.0;
-                const double mm = (double)M / (double)d.N;
-                rec.m2 = mm * mm;
-                rec.m4 = rec.m2 * rec.m2;
-                d.ring[slot] = rec;
-            }
+            if (slot < d.ring_cap) d.ring[slot] = ising_record(d, t, B, D);
         }
     }
 #undef PYRO_DOWN_OF
@@ -256,15 +287,7 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident_ising(Chain c)
     for (int j = 0; j < kCellsPerThread; ++j) {
         const int c0 = tid + j * NT;
         if (c0 >= ncell) continue;
-        const uint32_t m = SMK[c0];
-        uint32_t w[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            w[q] = 0;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) w[q] |= (((m >> (4 * q + b)) & 1u) ? 0xFFu : 0x01u) << (8 * b);
-        }
-        reinterpret_cast<int4 *>(d.spins)[c0] = make_int4((int)w[0], (int)w[1], (int)w[2], (int)w[3]);
+        reinterpret_cast<int4 *>(d.spins)[c0] = mask_spins(SMK[c0]);
     }
     if (tid == 0) {
         RepState ns;
@@ -276,18 +299,296 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident_ising(Chain c)
     }
 }
 
-hipError_t launch_resident_ising(const Chain &c, int maxL, hipStream_t st, const LaunchHook &hook)
+// -------------------------------------------------------- quad kernel ---
+// The same sweeps with four threads per cell, thread f = 0..3 owning the up
+// tetrahedron f of the cell (sites 4 f .. 4 f + 3) and the down tetrahedron
+// f, up to kQuadMaxL with a 32-bit forest.  One workgroup on one compute unit
+// is bound by the latency of its dependent steps, so each thread's chains are
+// short: one Philox block (threads 0..2 of the quad; the flags are shared by
+// DPP), 4 forest entries, at most 3 unions, 4 root walks side by side.  The
+// unions are balanced over each wave as in the tile pass.  Three barriers a
+// sweep:
+//   A  activation; the up tetrahedra seed the forest; bonds whose top byte
+//      ties are listed; the sweep's coins; aligned bonds of the incoming state
+//      (the energy of the previous record)
+//   B  unions of the down tetrahedra, then of the tied bonds, each a union of
+//      its own when its low draw activates it; the previous record
+//   C  root, coin and flip of every site; the magnetisation of the new state
+// Per sweep of a long call L = 8 takes 11 us and L = 12 34 us; with one cell per
+// thread and seven barriers (k_resident_ising) they took 23 and 48 us.
+namespace {
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t quad_perm(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+
+// Sum over the wave, valid in its lane 0.
+__device__ __forceinline__ int wave_sum(int v)
+{
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off, kWave);
+    return v;
+}
+
+}  // namespace
+
+template <int PASSES>
+__global__ __launch_bounds__(kResidentThreads) void k_quad_ising(Chain c, RepState armed, bool use_armed)
+{
+    extern __shared__ __align__(16) char lds[];
+    const int rep = blockIdx.x;
+    const RepState st = use_armed ? armed : *c.state[rep];
+    if (st.remaining <= 0) return;
+    const RepDesc &d = c.desc[rep];
+    const int L = d.L, ncell = (int)d.ncell, N = (int)d.N;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, f = tid & 3;
+    constexpr int NT = kResidentThreads;
+    const QuadLayout ly = quad_layout(L);
+    uint32_t *P = (uint32_t *)(lds + ly.p);
+    lds_byte *base = (lds_byte *)lds;
+    __attribute__((address_space(3))) int *sums = (__attribute__((address_space(3))) int *)(base + ly.sums);
+    __attribute__((address_space(3))) int *ties_n = (__attribute__((address_space(3))) int *)(base + ly.ties_n);
+    lds_word *CW = (lds_word *)(base + ly.cw);
+    lds_word *W = (lds_word *)(base + ly.un + 512 * wave);
+    lds_word *TI = (lds_word *)(base + ly.ties);
+    __attribute__((address_space(3))) volatile uint16_t *SMK = (__attribute__((address_space(3))) volatile uint16_t *)(base + ly.smk);
+    __attribute__((address_space(3))) volatile uint8_t *K4 = (__attribute__((address_space(3))) volatile uint8_t *)(base + ly.k4);
+
+    if (tid < 64) {
+        constexpr K4Table k4 = make_k4();
+        K4[tid] = k4.v[tid];
+    }
+    if (tid < 6) sums[tid] = 0;
+    if (tid < 2) ties_n[tid] = 0;
+    // Sites of the thread's down tetrahedra, 16 bits each.
+    uint32_t v01[PASSES], v23[PASSES];
+    int down = 0;  // down spins of the thread's sites in the incoming state
+#pragma unroll
+    for (int j = 0; j < PASSES; ++j) {
+        const int cell = (tid + j * NT) >> 2;
+        v01[j] = v23[j] = 0;
+        if (cell >= ncell) continue;
+        const CellNbrs nb = cell_neighbours(cell, L);
+        const int c1 = f == 0 ? nb.c[kMyMz] : f == 1 ? cell : f == 2 ? nb.c[kMy] : nb.c[kMz];
+        const int c2 = f == 0 ? nb.c[kMxMz] : f == 1 ? nb.c[kMx] : f == 2 ? cell : nb.c[kMz];
+        const int c3 = f == 0 ? nb.c[kMxMy] : f == 1 ? nb.c[kMx] : f == 2 ? nb.c[kMy] : cell;
+        // vertex mu of tetrahedron f is site 4 (f xor mu) + mu of its cell
+        v01[j] = (uint32_t)(16 * cell + 4 * f) | (uint32_t)(16 * c1 + 4 * (f ^ 1) + 1) << 16;
+        v23[j] = (uint32_t)(16 * c2 + 4 * (f ^ 2) + 2) | (uint32_t)(16 * c3 + 4 * (f ^ 3) + 3) << 16;
+        const uint32_t m = spin_mask16(reinterpret_cast<const int4 *>(d.spins)[cell]);
+        if (f == 0) SMK[cell] = (uint16_t)m;
+        down += __popc((m >> (4 * f)) & 15u);
+    }
+    __syncthreads();
+    // Spins of the thread's up (bits 0..3) and down (4..7) tetrahedra.
+    auto vertex_spins = [&](int j) {
+        auto bit = [&](uint32_t v) { return ((uint32_t)SMK[v >> 4] >> (v & 15u)) & 1u; };
+        const uint32_t a = v01[j] & 0xFFFFu, b = v01[j] >> 16, e = v23[j] & 0xFFFFu, g = v23[j] >> 16;
+        const uint32_t m = SMK[a >> 4];
+        return ((m >> (4 * f)) & 15u) | ((m >> (4 * f)) & 1u) << 4 | bit(b) << 5 | bit(e) << 6 | bit(g) << 7;
+    };
+    const uint32_t C = d.thr_hi * 0x01010101u;  // all parallel bonds are active from 256 on
+    const bool all = d.thr_hi >= 256u;
+    int cur = 0;  // set of sums that the state entering the sweep fills
+    for (int s = 0;; ++s) {
+        const bool end = s == st.remaining;  // only the sums of the last state remain
+        const uint32_t t = st.t + (uint32_t)s;
+        int aligned_n = 0;
+        uint8_t code[PASSES];
+#pragma unroll
+        for (int j = 0; j < PASSES; ++j) {
+            const int cell = (tid + j * NT) >> 2;
+            code[j] = 0xE4;
+            const bool valid = cell < ncell;
+            uint32_t al = 0;  // aligned bonds: up tetrahedron in bits 0..5, down in 6..11
+            if (valid) {
+                const uint32_t sp = vertex_spins(j);
+                al = (anti6(sp & 15u) | anti6(sp >> 4) << 6) ^ 0xFFFu;
+            }
+            aligned_n += __popc(al);
+            if (end) continue;
+            // Flags of the cell's 48 top bytes: thread q < 3 of the quad draws
+            // block q; every thread takes its 12 bits.
+            uint32_t act = al, tie = 0;
+            if (!all) {
+                const uint4 r = philox4x32_10(3u * (uint32_t)cell + (uint32_t)min(f, 2), t, kStreamBond, 0u, d.key);
+                const uint32_t lt = gather_flags16(bytes_lt(r.x, C), bytes_lt(r.y, C), bytes_lt(r.z, C), bytes_lt(r.w, C));
+                const uint32_t eq = gather_flags16(bytes_eq(r.x, C), bytes_eq(r.y, C), bytes_eq(r.z, C), bytes_eq(r.w, C));
+                const uint32_t w = lt | eq << 16;
+                const uint32_t w0 = quad_perm<0x00>(w), w1 = quad_perm<0x55>(w), w2 = quad_perm<0xAA>(w);
+                const uint64_t acc = (uint64_t)((w0 & 0xFFFFu) | w1 << 16) | (uint64_t)(w2 & 0xFFFFu) << 32;
+                const uint64_t eqs = (uint64_t)(w0 >> 16 | (w1 & 0xFFFF0000u)) | (uint64_t)(w2 >> 16) << 32;
+                act = al & ((uint32_t)(acc >> (6 * f) & 63u) | (uint32_t)(acc >> (24 + 6 * f) & 63u) << 6);
+                tie = al & ((uint32_t)(eqs >> (6 * f) & 63u) | (uint32_t)(eqs >> (24 + 6 * f) & 63u) << 6);
+            }
+            if (!valid) continue;
+            while (tie) {
+                const int k = __ffs((int)tie) - 1;
+                tie &= tie - 1;
+                const int e = k < 6 ? k : k - 6, a = pair_a(e), b = pair_b(e);
+                const uint32_t bond = 48u * (uint32_t)cell + 6u * (uint32_t)(k < 6 ? f : 4 + f) + (uint32_t)e;
+                auto vert = [&](int mu) {
+                    const uint32_t w = mu < 2 ? v01[j] : v23[j];
+                    return k < 6 ? (uint32_t)(16 * cell + 4 * f + mu) : ((mu & 1) ? w >> 16 : w & 0xFFFFu);
+                };
+                const int i = __hip_atomic_fetch_add(&ties_n[s & 1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (i < kQuadTies) {
+                    TI[2 * i] = bond;
+                    TI[2 * i + 1] = vert(a) << 16 | vert(b);
+                } else {  // beyond the list: decided here
+                    const uint4 lo = philox4x32_10(bond >> 2, t, kStreamBondLo, 0u, d.key);
+                    if ((word_of(lo, bond & 3u) & 0xFFFFFFu) < d.thr_lo) act |= 1u << k;
+                }
+            }
+            const uint32_t up = K4[act & 63u], b0 = 4u * (uint32_t)(16 * cell + 4 * f);
+            code[j] = K4[act >> 6];
+#pragma unroll
+            for (int mu = 0; mu < 4; ++mu) node(P, b0 + 4 * mu) = b0 + 4 * ((up >> (2 * mu)) & 3u);
+        }
+        if (!end)
+            for (int g = tid; g < (N + 127) / 128; g += NT) {
+                const uint4 w = philox4x32_10((uint32_t)g, t, kStreamFlip, 0u, d.key);
+                CW[4 * g] = w.x;
+                CW[4 * g + 1] = w.y;
+                CW[4 * g + 2] = w.z;
+                CW[4 * g + 3] = w.w;
+            }
+        {
+            const int a = wave_sum(aligned_n), m = wave_sum(down);
+            if (lane == 0) {
+                __hip_atomic_fetch_add(&sums[2 * cur], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add(&sums[2 * cur + 1], a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+        __syncthreads();
+        // The record of the state entering the sweep (of a tiled sweep before
+        // this call when s = 0); the third set of sums is cleared for the next.
+        const int next = cur == 2 ? 0 : cur + 1, clear = next == 2 ? 0 : next + 1;
+        if (tid == NT - 1) {
+            const int slot = s == 0 ? st.e_pending : st.ring_used + s - 1;
+            if (slot >= 0 && slot < d.ring_cap)
+                d.ring[slot] = ising_record(d, t - 1, 2 * (int64_t)sums[2 * cur + 1] - 3 * (int64_t)N, sums[2 * cur]);
+            sums[2 * clear] = 0;
+            sums[2 * clear + 1] = 0;
+            ties_n[(s + 1) & 1] = 0;
+        }
+        if (end) break;
+        // Unions, balanced over the wave (see tile_components).
+        int n = 0;
+        auto unite_row = [&](int m) {
+            wave_sync();
+            if (lane < m) {
+                const uint32_t u = W[lane];
+                lds_unite(P, (u >> 14) & ~3u, (u & 0xFFFFu) << 2);
+            }
+        };
+#pragma unroll
+        for (int j = 0; j < PASSES; ++j) {
+#pragma unroll
+            for (int mu = 1; mu < 4; ++mu) {
+                const uint32_t rp = ((uint32_t)code[j] >> (2 * mu)) & 3u;
+                const uint32_t kr = rp == 0 ? v01[j] & 0xFFFFu : (rp == 1 ? v01[j] >> 16 : v23[j] & 0xFFFFu);
+                const uint32_t km = mu == 1 ? v01[j] >> 16 : (mu == 2 ? v23[j] & 0xFFFFu : v23[j] >> 16);
+                const bool use = rp != (uint32_t)mu;
+                const uint64_t b = __ballot(use);
+                const int at = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+                if (use) W[at] = kr << 16 | km;
+                n += (int)__popcll(b);
+                if (n >= 64) {
+                    unite_row(64);
+                    const uint32_t rest = W[64 + lane];
+                    wave_sync();
+                    W[lane] = rest;
+                    wave_sync();
+                    n -= 64;
+                }
+            }
+        }
+        unite_row(n);
+        const int nt = min((int)ties_n[s & 1], kQuadTies);
+        for (int i = tid; i < nt; i += NT) {
+            const uint32_t bond = TI[2 * i], u = TI[2 * i + 1];
+            const uint4 lo = philox4x32_10(bond >> 2, t, kStreamBondLo, 0u, d.key);
+            if ((word_of(lo, bond & 3u) & 0xFFFFFFu) < d.thr_lo) lds_unite(P, (u >> 14) & ~3u, (u & 0xFFFFu) << 2);
+        }
+        __syncthreads();
+        const bool last = s + 1 == st.remaining;
+        down = 0;
+#pragma unroll
+        for (int j = 0; j < PASSES; ++j) {
+            const int cell = (tid + j * NT) >> 2;
+            uint32_t fl = 0, m = 0;
+            if (cell < ncell) {
+                const uint32_t b0 = 4u * (uint32_t)(16 * cell + 4 * f);
+                uint32_t r[4], moved;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) r[k] = node(P, b0 + 4 * k);
+                do {
+                    moved = 0;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const uint32_t p = node(P, r[k]);
+                        moved |= p ^ r[k];
+                        r[k] = p;
+                    }
+                } while (moved);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) fl |= __builtin_amdgcn_ubfe(CW[r[k] >> 7], (r[k] >> 2) & 31u, 1u) << k;
+                if (last)
+                    reinterpret_cast<int4 *>(d.label)[4 * cell + f] =
+                        make_int4((int)(r[0] >> 2), (int)(r[1] >> 2), (int)(r[2] >> 2), (int)(r[3] >> 2));
+                m = SMK[cell];
+            }
+            uint32_t w = fl << (4 * f);
+            w |= quad_perm<0xB1>(w);  // threads 1, 0, 3, 2
+            w |= quad_perm<0x4E>(w);  // threads 2, 3, 0, 1
+            m ^= w;
+            if (cell < ncell) {
+                down += __popc((m >> (4 * f)) & 15u);
+                if (f == 0) SMK[cell] = (uint16_t)m;
+                if (last && f == 0) reinterpret_cast<int4 *>(d.spins)[cell] = mask_spins(m);
+            }
+        }
+        __syncthreads();
+        cur = next;
+    }
+    if (tid == 0) c.state[rep][0] = RepState{st.t + (uint32_t)st.remaining, 0, st.ring_used + st.remaining, -1};
+}
+
+template <int PASSES>
+static hipError_t launch_quad(const Chain &c, int maxL, const RepState &armed, bool use_armed, hipStream_t st)
+{
+    static const hipError_t attr = hipFuncSetAttribute((const void *)k_quad_ising<PASSES>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                       (int)quad_layout(kQuadMaxL).total);
+    if (attr != hipSuccess) return attr;
+    k_quad_ising<PASSES><<<c.nreps, kResidentThreads, quad_layout(maxL).total, st>>>(c, armed, use_armed);
+    return hipSuccess;
+}
+
+hipError_t launch_resident_ising(const Chain &c, int maxL, const RepState *armed, hipStream_t st, const LaunchHook &hook)
 {
     if (c.nreps == 0) return hipSuccess;
-    if (maxL < 1 || maxL > kResidentMaxL) return hipErrorInvalidValue;
-    static const hipError_t attr = hipFuncSetAttribute(
-        (const void *)k_resident_ising, hipFuncAttributeMaxDynamicSharedMemorySize, (int)resident_layout(kResidentMaxL).total);
-    if (attr != hipSuccess) return attr;
-    const size_t lds = resident_layout(maxL).total;
+    if (maxL < 1 || maxL > kResidentMaxL || (armed && c.nreps != 1)) return hipErrorInvalidValue;
+    const RepState from = armed ? *armed : RepState{};
+    const int tets = 4 * maxL * maxL * maxL, passes = (tets + kResidentThreads - 1) / kResidentThreads;
+    hipError_t e = hipSuccess;
     if (hook.before) hook.before(hook.ctx, kKResident);
-    k_resident_ising<<<c.nreps, kResidentThreads, lds, st>>>(c);
+    if (maxL > kQuadMaxL) {
+        static const hipError_t attr = hipFuncSetAttribute(
+            (const void *)k_resident_ising, hipFuncAttributeMaxDynamicSharedMemorySize, (int)resident_layout(kResidentMaxL).total);
+        e = attr;
+        if (e == hipSuccess)
+            k_resident_ising<<<c.nreps, kResidentThreads, resident_layout(maxL).total, st>>>(c, from, armed != nullptr);
+    } else if (passes <= 1) e = launch_quad<1>(c, maxL, from, armed != nullptr, st);
+    else if (passes <= 2) e = launch_quad<2>(c, maxL, from, armed != nullptr, st);
+    else if (passes <= 4) e = launch_quad<4>(c, maxL, from, armed != nullptr, st);
+    else if (passes <= 7) e = launch_quad<7>(c, maxL, from, armed != nullptr, st);
+    else e = launch_quad<9>(c, maxL, from, armed != nullptr, st);
     if (hook.after) hook.after(hook.ctx, kKResident);
-    return hipGetLastError();
+    return e == hipSuccess ? hipGetLastError() : e;
 }
 
 }  // namespace pyro
