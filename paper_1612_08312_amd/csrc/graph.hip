@@ -2,14 +2,14 @@
 // table): the paper's remark that the algorithm carries over to other
 // lattices once a nearest-neighbour table is supplied (Sec. 2, Sec. 4).
 //
-// No lattice tiles: windows of 4096 sites, and one thread per bond or per
-// site.  Per sweep:
-//   O(n) only  k_graph_prepare    sigma_i = s_i . r (each workgroup draws the
-//                                 sweep's embedding axis r itself)
-//              k_graph_local      sites cut into windows of 4096, one
-//                                 workgroup each: activation of the bonds with
-//                                 both ends in the window and their union in
-//                                 LDS; every site stores its local root
+// No lattice tiles: windows of 512 to 4096 sites, and one thread per bond or
+// per site.  Per sweep:
+//              k_graph_local      sites cut into windows, one workgroup each:
+//                                 O(n) sigma_i = s_i . r (each lane draws the
+//                                 sweep's embedding axis r itself); activation
+//                                 of the bonds with both ends in the window
+//                                 and their union in LDS; every site stores
+//                                 its local root
 //              k_graph_cross      activation of the bonds between windows and
 //                                 union of their ends in the global forest
 //                                 (index linking: the larger root is hooked
@@ -55,13 +55,14 @@ constexpr int kGraphRing = 1024;  // device records between drains
 struct GraphDesc {
     int64_t N, NB;
     int64_t n_cross;  // bonds between windows (the last n_cross of the bond arrays)
+    int window;       // sites per window
     int n;  // 1 Ising, 2 XY, 3 Heisenberg
     const int32_t *ba, *bb;  // bond ends: bonds inside one site window first, grouped by window,
                              // then the bonds between windows
     const uint32_t *bond_id; // position of each bond in the caller's table (keys its draws)
     const int64_t *wstart;   // [nwin + 1] first bond of each window; wstart[nwin] = first bond between windows
-    const int32_t *wsite;    // [N] window w holds the sites wsite[w kWindow ..], ascending within the
-                             // window; NULL: window w holds the indices w kWindow ..
+    const int32_t *wsite;    // [N] window w holds the sites wsite[w window ..], ascending within the
+                             // window; NULL: window w holds the indices w window ..
     const uint16_t *la, *lb; // bonds inside a window: positions of their ends in the window
     void *spins;  // int8 [N] or float [n][N]
     int32_t *label;
@@ -77,9 +78,15 @@ struct GraphDesc {
     PhiloxKey key;
 };
 
+// Entries are read at workgroup scope, which the caches may serve stale
+// within a launch (agent-scope loads went past the L2 on every step).  A stale
+// entry is an older value of it, an ancestor of the node in the final forest,
+// so a walk over stale entries ends at a node of the right tree; whether that
+// is still a root is decided by the compare-and-swap, which returns the
+// current value.
 __device__ __forceinline__ int32_t lab_get(const int32_t *lab, int32_t x)
 {
-    return __hip_atomic_load(const_cast<int32_t *>(lab) + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_load(const_cast<int32_t *>(lab) + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Root of x: parents are never larger than their children, so the chase
@@ -96,16 +103,22 @@ __device__ __forceinline__ int32_t graph_root(const int32_t *lab, int32_t x)
     }
 }
 
+// Union of the trees of a and b: a root may be hooked under any smaller node
+// (which cannot lie in its own tree), so b is walked only when a's root is
+// the smaller of the two.
 __device__ void graph_unite(int32_t *lab, int32_t a, int32_t b)
 {
     for (;;) {
         a = graph_root(lab, a);
-        b = graph_root(lab, b);
         if (a == b) return;
         if (a < b) {
-            const int32_t t = a;
-            a = b;
-            b = t;
+            b = graph_root(lab, b);
+            if (a == b) return;
+            if (a < b) {
+                const int32_t t = a;
+                a = b;
+                b = t;
+            }
         }
         int32_t expected = a;
         if (__hip_atomic_compare_exchange_strong(lab + a, &expected, b, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
@@ -128,18 +141,6 @@ __device__ __forceinline__ void graph_axis(const GraphDesc &g, uint32_t t, float
 {
     if (threadIdx.x == 0) unit_vector(0u, t, kStreamAxis, g.n, g.key, ax);
     __syncthreads();
-}
-
-__global__ __launch_bounds__(kBlock) void k_graph_prepare(GraphDesc g, uint32_t t)
-{
-    __shared__ float ax[3];
-    graph_axis(g, t, ax);
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= g.N) return;
-    const float *s = (const float *)g.spins;
-    const float r[3] = {ax[0], ax[1], ax[2]};
-    const float v[3] = {s[i], s[g.N + i], g.n == 3 ? s[2 * g.N + i] : 0.0f};
-    g.sigma[i] = g.n == 2 ? project<2>(v, r) : project<3>(v, r);
 }
 
 // Activation of bond b (its position in the caller's table) between sites
@@ -181,12 +182,15 @@ __device__ __forceinline__ void add_bond_sum(const GraphDesc &g, int64_t e, int6
         __hip_atomic_fetch_add(g.eacc, (unsigned long long)bs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Sites are cut into windows of kWindow sites (the last may hold fewer):
+// Sites are cut into windows of g.window sites (the last may hold fewer):
 // either consecutive indices, or, where that cuts fewer bonds, balls grown
 // breadth first over the bond table (set-up, graph_windows).  Bonds with
 // both ends in one window are grouped (at set-up) by window.
-constexpr int kWindow = 4096;
 constexpr int kLocalThreads = 512;  // threads of the window pass
+// Sites per window of a graph of n sites: a large graph's windows keep most
+// bonds off the global forest; a small one's are cut down until its window
+// pass has a workgroup for most compute units.
+inline int window_of(int64_t n) { return n >= (1 << 20) ? 4096 : n >= (1 << 19) ? 2048 : n >= (1 << 17) ? 1024 : 512; }
 
 __device__ __forceinline__ int lds_root(const int *P, int x)
 {
@@ -200,7 +204,9 @@ __device__ __forceinline__ int lds_root(const int *P, int x)
 // One workgroup per window: union of the active bonds with both ends in the
 // window in LDS (index linking with atomic min, so each local root is the
 // smallest site of its local component), then every site of the window
-// stores the global index of its local root.
+// stores the global index of its local root.  O(n): the projections of the
+// window's sites on the sweep's axis first, kept for the later passes.
+template <int kWindow>
 __global__ __launch_bounds__(kLocalThreads) void k_graph_local(GraphDesc g, uint32_t t)
 {
     __shared__ int P[kWindow];
@@ -209,10 +215,20 @@ __global__ __launch_bounds__(kLocalThreads) void k_graph_local(GraphDesc g, uint
     const int64_t base = (int64_t)blockIdx.x * kWindow;
     const int nloc = (int)std::min<int64_t>(kWindow, g.N - base);
     const int32_t *ws = g.wsite ? g.wsite + base : nullptr;  // uniform
+    float r[3] = {0.0f, 0.0f, 0.0f};
+    if (g.n > 1) unit_vector(0u, t, kStreamAxis, g.n, g.key, r);  // the same in every lane
     for (int k = threadIdx.x; k < nloc; k += kLocalThreads) {
         const int64_t i = ws ? (int64_t)ws[k] : base + k;
         P[k] = k;
-        SG[k] = g.n == 1 ? (float)((const int8_t *)g.spins)[i] : g.sigma[i];
+        if (g.n == 1) {
+            SG[k] = (float)((const int8_t *)g.spins)[i];
+        } else {
+            const float *s = (const float *)g.spins;
+            const float v[3] = {s[i], s[g.N + i], g.n == 3 ? s[2 * g.N + i] : 0.0f};
+            const float sig = g.n == 2 ? project<2>(v, r) : project<3>(v, r);
+            SG[k] = sig;
+            g.sigma[i] = sig;
+        }
     }
     __syncthreads();
     const int64_t b1 = g.wstart[blockIdx.x + 1];
@@ -264,7 +280,7 @@ __global__ __launch_bounds__(kLocalThreads) void k_graph_local(GraphDesc g, uint
 __global__ __launch_bounds__(kBlock) void k_graph_cross(GraphDesc g, uint32_t t)
 {
     __shared__ int64_t red[16];
-    const int64_t first = g.wstart[(g.N + kWindow - 1) / kWindow];
+    const int64_t first = g.wstart[(g.N + g.window - 1) / g.window];
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     int64_t e = 0;
     for (int64_t q = first + (int64_t)blockIdx.x * kBlock + threadIdx.x; q < g.NB; q += stride) {
@@ -417,11 +433,11 @@ hipError_t launch_graph_bond_total(const GraphDesc &g, hipStream_t st)
 
 hipError_t launch_graph_sweep(const GraphDesc &g, uint32_t t, int slot, hipStream_t st)
 {
-    const int nsb = blocks_for(g.N), nbb = blocks_for(g.NB);
-    if (g.n > 1) {
-        k_graph_prepare<<<nsb, kBlock, 0, st>>>(g, t);
-    }
-    k_graph_local<<<blocks_for(g.N, kWindow), kLocalThreads, 0, st>>>(g, t);
+    const int nbb = blocks_for(g.NB), nwin = blocks_for(g.N, g.window);
+    if (g.window == 4096) k_graph_local<4096><<<nwin, kLocalThreads, 0, st>>>(g, t);
+    else if (g.window == 2048) k_graph_local<2048><<<nwin, kLocalThreads, 0, st>>>(g, t);
+    else if (g.window == 1024) k_graph_local<1024><<<nwin, kLocalThreads, 0, st>>>(g, t);
+    else k_graph_local<512><<<nwin, kLocalThreads, 0, st>>>(g, t);
     // the cross pass writes no partials (its bond sum goes to an atomic), so
     // its grid may exceed kPartBlocks: more bonds in flight hide the chases
     if (g.n_cross > 0)
@@ -523,7 +539,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // order, win gives each site's window and pos its position in it; otherwise
 // all three are left empty.  Windows change the work split only: labels are
 // canonical and every draw is keyed by bond, site and sweep.
-void graph_windows(int64_t N, int64_t NB, const int32_t *ba, const int32_t *bb, std::vector<int32_t> &wsite,
+void graph_windows(int64_t N, int64_t NB, int kWindow, const int32_t *ba, const int32_t *bb, std::vector<int32_t> &wsite,
                    std::vector<int32_t> &win, std::vector<uint16_t> &pos)
 {
     if (N <= kWindow || NB == 0) return;
@@ -623,11 +639,12 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
     // sort), then the bonds between windows in table order; bond_id keeps
     // each one's position in the caller's table, and la / lb the positions of
     // an inside bond's ends in its window.
+    const int kWindow = window_of(n_sites);
     const int64_t nwin = (n_sites + kWindow - 1) / kWindow;
     std::vector<int32_t> wsite, win;
     std::vector<uint16_t> pos;
     try {
-        graph_windows(n_sites, n_bonds, bond_a, bond_b, wsite, win, pos);
+        graph_windows(n_sites, n_bonds, kWindow, bond_a, bond_b, wsite, win, pos);
     } catch (const std::bad_alloc &) {  // no host memory for the balls: consecutive windows
         wsite.clear();
         win.clear();
@@ -698,6 +715,7 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
     d.N = n_sites;
     d.NB = n_bonds;
     d.n_cross = n_bonds - n_inside;
+    d.window = kWindow;
     d.n = model;
     d.ba = (const int32_t *)(g->mem + off[0]);
     d.bb = (const int32_t *)(g->mem + off[1]);
