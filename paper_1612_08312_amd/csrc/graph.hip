@@ -51,6 +51,8 @@ namespace pyro {
 namespace {
 
 constexpr int kGraphRing = 1024;  // device records between drains
+// One word for all blocks of the union passes serialised their additions.
+constexpr int kAccLines = 64, kAccStride = 16;  // words (128 bytes) apart
 
 struct GraphDesc {
     int64_t N, NB;
@@ -71,7 +73,8 @@ struct GraphDesc {
     double *dpart;   // O(n) partials: [kPartBlocks bond blocks][3][kPartBlocks site blocks]
     DevRecord *ring;
     unsigned long long *eacc;  // Ising: bond sum of the state entering the sweep, summed by the union
-                               // passes; the finalize moves it into the record and clears it
+                               // passes into kAccLines words of a line each; the finalize moves their
+                               // sum into the record and clears them
     uint32_t thr_hi, thr_lo;  // Ising threshold split at bit 24
     float x0;
     double J;
@@ -179,7 +182,7 @@ __device__ __forceinline__ void add_bond_sum(const GraphDesc &g, int64_t e, int6
     if (g.n != 1) return;
     const int64_t bs = block_sum<int64_t>(e, red);
     if (threadIdx.x == 0 && bs != 0)
-        __hip_atomic_fetch_add(g.eacc, (unsigned long long)bs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(g.eacc + kAccStride * (blockIdx.x % kAccLines), (unsigned long long)bs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Sites are cut into windows of g.window sites (the last may hold fewer):
@@ -382,9 +385,14 @@ __global__ __launch_bounds__(kBlock) void k_graph_finalize(GraphDesc g, uint32_t
         int64_t M = 0;
         for (int k = threadIdx.x; k < nsp; k += kBlock) M += g.ipart[kPartBlocks + k];
         M = block_sum<int64_t>(M, ired);
+        int64_t B = 0;
+        if (threadIdx.x < kAccLines) {
+            B = (int64_t)g.eacc[kAccStride * threadIdx.x];
+            g.eacc[kAccStride * threadIdx.x] = 0ull;
+        }
+        B = block_sum<int64_t>(B, ired);
         if (threadIdx.x == 0) {
-            r.reserved = (int64_t)*g.eacc;
-            *g.eacc = 0ull;
+            r.reserved = B;
             r.M_int = M;
             r.M[0] = (double)M;
             const double mm = (double)M / (double)g.N;
@@ -687,7 +695,7 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
                                   sizeof(int32_t) * (size_t)n_sites, model == PYRO_ISING ? 0 : sizeof(float) * (size_t)n_sites,
                                   sizeof(int64_t) * 2 * kPartBlocks, sizeof(double) * 4 * kPartBlocks,
                                   sizeof(DevRecord) * (kGraphRing + 1), sizeof(uint32_t) * (size_t)n_bonds,
-                                  sizeof(int64_t) * (size_t)(nwin + 1), sizeof(unsigned long long),
+                                  sizeof(int64_t) * (size_t)(nwin + 1), sizeof(unsigned long long) * kAccLines * kAccStride,
                                   sizeof(int32_t) * wsite.size(), sizeof(uint16_t) * (size_t)n_inside,
                                   sizeof(uint16_t) * (size_t)n_inside};
     for (int k = 0; k < kParts; ++k) {
@@ -735,7 +743,7 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
     d.key = philox_key(seed);
     graph_params(g, T);
     hipError_t e = hipMemcpy((void *)d.wstart, wstart.data(), sizeof(int64_t) * wstart.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(d.eacc, 0, sizeof(unsigned long long));
+    if (e == hipSuccess) e = hipMemset(d.eacc, 0, sizeof(unsigned long long) * kAccLines * kAccStride);
     if (e == hipSuccess && balls)
         e = hipMemcpy((void *)d.wsite, wsite.data(), sizeof(int32_t) * wsite.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && n_inside > 0)
