@@ -54,6 +54,11 @@ constexpr int kGraphRing = 1024;  // device records between drains
 // One word for all blocks of the union passes serialised their additions.
 constexpr int kAccLines = 64, kAccStride = 16;  // words (128 bytes) apart
 
+constexpr int kDrawChunk = 1024;  // Philox blocks a window pass keeps in LDS at a time
+struct DrawChunk {
+    int64_t bond, block;
+};
+
 struct GraphDesc {
     int64_t N, NB;
     int64_t n_cross;  // bonds between windows (the last n_cross of the bond arrays)
@@ -66,6 +71,15 @@ struct GraphDesc {
     const int32_t *wsite;    // [N] window w holds the sites wsite[w window ..], ascending within the
                              // window; NULL: window w holds the indices w window ..
     const uint16_t *la, *lb; // bonds inside a window: positions of their ends in the window
+    // Ising with shared draws (dblock not NULL): the distinct Philox blocks of
+    // each window's bonds, cut into chunks of kDrawChunk; chunk k of the graph
+    // holds the blocks from dchunk[k].block and the bonds from dchunk[k].bond
+    // on, window w the chunks from wchunk[w] on, and dslot is each inside
+    // bond's byte in its chunk
+    const uint32_t *dblock;
+    const struct DrawChunk *dchunk;
+    const int32_t *wchunk;
+    const uint16_t *dslot;
     void *spins;  // int8 [N] or float [n][N]
     int32_t *label;
     float *sigma;  // O(n) projections [N]
@@ -146,6 +160,13 @@ __device__ __forceinline__ void graph_axis(const GraphDesc &g, uint32_t t, float
     __syncthreads();
 }
 
+// Low draw of bond b, whose top byte ties, in sweep t.
+__device__ __forceinline__ bool ising_tie_active(const GraphDesc &g, uint32_t b, uint32_t t)
+{
+    const uint4 v = philox4x32_10(b >> 2, t, kStreamBondLo, 0u, g.key);
+    return (word_of(v, b & 3u) & 0xFFFFFFu) < g.thr_lo;
+}
+
 // Activation of bond b (its position in the caller's table) between sites
 // i and j in sweep t.
 __device__ __forceinline__ bool ising_bond_active(const GraphDesc &g, uint32_t b, int8_t si, int8_t sj, uint32_t t)
@@ -155,8 +176,7 @@ __device__ __forceinline__ bool ising_bond_active(const GraphDesc &g, uint32_t b
     const uint32_t k = b & 15u;
     const uint32_t hi = (word_of(w, k >> 2) >> (8 * (k & 3u))) & 0xFFu;
     if (hi != g.thr_hi) return hi < g.thr_hi;
-    const uint4 v = philox4x32_10(b >> 2, t, kStreamBondLo, 0u, g.key);
-    return (word_of(v, b & 3u) & 0xFFFFFFu) < g.thr_lo;
+    return ising_tie_active(g, b, t);
 }
 
 // Activation of bond b between sites i and j; for Ising, *e gains s_i s_j of
@@ -204,26 +224,51 @@ __device__ __forceinline__ int lds_root(const int *P, int x)
     }
 }
 
+// Union of window positions a and b (index linking with atomic min, so each
+// local root is the smallest position, hence site, of its component).
+__device__ __forceinline__ void lds_link(int *P, int a, int b)
+{
+    for (;;) {
+        a = lds_root(P, a);
+        b = lds_root(P, b);
+        if (a == b) return;
+        if (a < b) {
+            const int x = a;
+            a = b;
+            b = x;
+        }
+        const int old = __hip_atomic_fetch_min(P + a, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (old == a) return;
+        a = old;
+    }
+}
+
 // One workgroup per window: union of the active bonds with both ends in the
-// window in LDS (index linking with atomic min, so each local root is the
-// smallest site of its local component), then every site of the window
-// stores the global index of its local root.  O(n): the projections of the
-// window's sites on the sweep's axis first, kept for the later passes.
-template <int kWindow>
+// window in LDS, then every site of the window stores the global index of its
+// local root.  O(n): the projections of the window's sites on the sweep's axis
+// first, kept for the later passes.  Shared draws (Ising): the window's
+// Philox blocks are drawn once each into LDS, a chunk at a time, and a bond
+// reads its byte; drawn per bond, 16 bonds of a block made the pass spend two
+// thirds of its instructions on them.
+template <int kWindow, bool kShared>
 __global__ __launch_bounds__(kLocalThreads) void k_graph_local(GraphDesc g, uint32_t t)
 {
     __shared__ int P[kWindow];
-    __shared__ float SG[kWindow];  // the window's spins (Ising, as float) or projections (O(n))
+    __shared__ float SG[kShared ? 1 : kWindow];     // the window's spins (Ising, as float) or projections (O(n))
+    __shared__ int8_t SP[kShared ? kWindow : 1];    // the window's spins
+    __shared__ uint4 DR[kShared ? kDrawChunk : 1];  // the chunk's blocks
     __shared__ int64_t red[16];
     const int64_t base = (int64_t)blockIdx.x * kWindow;
     const int nloc = (int)std::min<int64_t>(kWindow, g.N - base);
     const int32_t *ws = g.wsite ? g.wsite + base : nullptr;  // uniform
     float r[3] = {0.0f, 0.0f, 0.0f};
-    if (g.n > 1) unit_vector(0u, t, kStreamAxis, g.n, g.key, r);  // the same in every lane
+    if (!kShared && g.n > 1) unit_vector(0u, t, kStreamAxis, g.n, g.key, r);  // the same in every lane
     for (int k = threadIdx.x; k < nloc; k += kLocalThreads) {
         const int64_t i = ws ? (int64_t)ws[k] : base + k;
         P[k] = k;
-        if (g.n == 1) {
+        if (kShared) {
+            SP[k] = ((const int8_t *)g.spins)[i];
+        } else if (g.n == 1) {
             SG[k] = (float)((const int8_t *)g.spins)[i];
         } else {
             const float *s = (const float *)g.spins;
@@ -233,36 +278,43 @@ __global__ __launch_bounds__(kLocalThreads) void k_graph_local(GraphDesc g, uint
             g.sigma[i] = sig;
         }
     }
-    __syncthreads();
-    const int64_t b1 = g.wstart[blockIdx.x + 1];
     int64_t e = 0;
-    for (int64_t q = g.wstart[blockIdx.x] + threadIdx.x; q < b1; q += kLocalThreads) {
-        int a = g.la[q], b = g.lb[q];
-        const float vi = SG[a], vj = SG[b];
-        const uint32_t bid = g.bond_id[q];
-        bool active;
-        if (g.n == 1) {
-            const int8_t si = (int8_t)vi, sj = (int8_t)vj;
-            e += (int64_t)si * (int64_t)sj;
-            active = ising_bond_active(g, bid, si, sj, t);
-        } else {
-            const float x = __fmul_rn(__fmul_rn(g.x0, vi), vj);
-            const uint4 w = philox4x32_10(bid >> 2, t, kStreamBond, 0u, g.key);
-            active = on_bond_active(x, word_of(w, bid & 3u));
-        }
-        if (!active) continue;
-        for (;;) {
-            a = lds_root(P, a);
-            b = lds_root(P, b);
-            if (a == b) break;
-            if (a < b) {
-                const int x = a;
-                a = b;
-                b = x;
+    if constexpr (kShared) {
+        const uint8_t *bytes = reinterpret_cast<const uint8_t *>(DR);
+        for (int ck = g.wchunk[blockIdx.x]; ck < g.wchunk[blockIdx.x + 1]; ++ck) {
+            const DrawChunk c0 = g.dchunk[ck], c1 = g.dchunk[ck + 1];
+            __syncthreads();  // the spins, or the last chunk, are done with
+            for (int k = threadIdx.x; k < (int)(c1.block - c0.block); k += kLocalThreads)
+                DR[k] = philox4x32_10(g.dblock[c0.block + k], t, kStreamBond, 0u, g.key);
+            __syncthreads();
+            for (int64_t q = c0.bond + threadIdx.x; q < c1.bond; q += kLocalThreads) {
+                const int a = g.la[q], b = g.lb[q];
+                const int8_t si = SP[a], sj = SP[b];
+                const uint32_t hi = bytes[g.dslot[q]];
+                e += (int64_t)si * (int64_t)sj;
+                if (si != sj || si == 0 || hi > g.thr_hi) continue;
+                if (hi == g.thr_hi && !ising_tie_active(g, g.bond_id[q], t)) continue;
+                lds_link(P, a, b);
             }
-            const int old = __hip_atomic_fetch_min(P + a, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (old == a) break;
-            a = old;
+        }
+    } else {
+        __syncthreads();
+        const int64_t b1 = g.wstart[blockIdx.x + 1];
+        for (int64_t q = g.wstart[blockIdx.x] + threadIdx.x; q < b1; q += kLocalThreads) {
+            const int a = g.la[q], b = g.lb[q];
+            const float vi = SG[a], vj = SG[b];
+            const uint32_t bid = g.bond_id[q];
+            bool active;
+            if (g.n == 1) {
+                const int8_t si = (int8_t)vi, sj = (int8_t)vj;
+                e += (int64_t)si * (int64_t)sj;
+                active = ising_bond_active(g, bid, si, sj, t);
+            } else {
+                const float x = __fmul_rn(__fmul_rn(g.x0, vi), vj);
+                const uint4 w = philox4x32_10(bid >> 2, t, kStreamBond, 0u, g.key);
+                active = on_bond_active(x, word_of(w, bid & 3u));
+            }
+            if (active) lds_link(P, a, b);
         }
     }
     __syncthreads();
@@ -276,6 +328,14 @@ __global__ __launch_bounds__(kLocalThreads) void k_graph_local(GraphDesc g, uint
             g.label[base + k] = (int32_t)(base + r);
     }
     add_bond_sum(g, e, red);
+}
+
+template <int kWindow>
+void launch_graph_local(const GraphDesc &g, uint32_t t, hipStream_t st)
+{
+    const int nwin = blocks_for(g.N, kWindow);
+    if (g.dblock) k_graph_local<kWindow, true><<<nwin, kLocalThreads, 0, st>>>(g, t);
+    else k_graph_local<kWindow, false><<<nwin, kLocalThreads, 0, st>>>(g, t);
 }
 
 // Bonds whose ends lie in different windows: union in the global forest of
@@ -441,11 +501,11 @@ hipError_t launch_graph_bond_total(const GraphDesc &g, hipStream_t st)
 
 hipError_t launch_graph_sweep(const GraphDesc &g, uint32_t t, int slot, hipStream_t st)
 {
-    const int nbb = blocks_for(g.NB), nwin = blocks_for(g.N, g.window);
-    if (g.window == 4096) k_graph_local<4096><<<nwin, kLocalThreads, 0, st>>>(g, t);
-    else if (g.window == 2048) k_graph_local<2048><<<nwin, kLocalThreads, 0, st>>>(g, t);
-    else if (g.window == 1024) k_graph_local<1024><<<nwin, kLocalThreads, 0, st>>>(g, t);
-    else k_graph_local<512><<<nwin, kLocalThreads, 0, st>>>(g, t);
+    const int nbb = blocks_for(g.NB);
+    if (g.window == 4096) launch_graph_local<4096>(g, t, st);
+    else if (g.window == 2048) launch_graph_local<2048>(g, t, st);
+    else if (g.window == 1024) launch_graph_local<1024>(g, t, st);
+    else launch_graph_local<512>(g, t, st);
     // the cross pass writes no partials (its bond sum goes to an atomic), so
     // its grid may exceed kPartBlocks: more bonds in flight hide the chases
     if (g.n_cross > 0)
@@ -689,7 +749,46 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
     win.shrink_to_fit();
     pos.clear();
     pos.shrink_to_fit();
-    constexpr int kParts = 14;
+    // Shared draws: a window's inside bonds are in table order, so the bonds
+    // of a Philox block (16 consecutive positions) follow one another.  Used
+    // where a block serves two of a window's bonds or more on average (a
+    // lattice numbered row by row: 8 or more), else each bond draws its own.
+    std::vector<uint32_t> hblock;
+    std::vector<DrawChunk> hchunk;
+    std::vector<int32_t> hwchunk;
+    std::vector<uint16_t> hslot;
+    if (model == PYRO_ISING && n_inside > 0) {
+        hslot.resize((size_t)n_inside);
+        hwchunk.resize((size_t)nwin + 1);
+        for (int64_t w = 0; w < nwin; ++w) {
+            hwchunk[(size_t)w] = (int32_t)hchunk.size();
+            int fill = kDrawChunk;  // blocks in the open chunk
+            uint32_t last = 0;
+            for (int64_t q = wstart[(size_t)w]; q < wstart[(size_t)w + 1]; ++q) {
+                const uint32_t blk = gid[(size_t)q] >> 4;
+                if (q == wstart[(size_t)w] || blk != last) {
+                    if (fill == kDrawChunk) {
+                        hchunk.push_back({q, (int64_t)hblock.size()});
+                        fill = 0;
+                    }
+                    hblock.push_back(blk);
+                    ++fill;
+                    last = blk;
+                }
+                hslot[(size_t)q] = (uint16_t)(16 * (fill - 1) + (int)(gid[(size_t)q] & 15u));
+            }
+        }
+        hwchunk[(size_t)nwin] = (int32_t)hchunk.size();
+        hchunk.push_back({n_inside, (int64_t)hblock.size()});
+    }
+    const bool shared = !hblock.empty() && 2 * (int64_t)hblock.size() <= n_inside;
+    if (!shared) {
+        hblock.clear();
+        hchunk.clear();
+        hwchunk.clear();
+        hslot.clear();
+    }
+    constexpr int kParts = 18;
     size_t off[kParts], total = 0;
     const size_t sizes[kParts] = {sizeof(int32_t) * (size_t)n_bonds, sizeof(int32_t) * (size_t)n_bonds, spin_bytes,
                                   sizeof(int32_t) * (size_t)n_sites, model == PYRO_ISING ? 0 : sizeof(float) * (size_t)n_sites,
@@ -697,7 +796,9 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
                                   sizeof(DevRecord) * (kGraphRing + 1), sizeof(uint32_t) * (size_t)n_bonds,
                                   sizeof(int64_t) * (size_t)(nwin + 1), sizeof(unsigned long long) * kAccLines * kAccStride,
                                   sizeof(int32_t) * wsite.size(), sizeof(uint16_t) * (size_t)n_inside,
-                                  sizeof(uint16_t) * (size_t)n_inside};
+                                  sizeof(uint16_t) * (size_t)n_inside, sizeof(uint32_t) * hblock.size(),
+                                  sizeof(DrawChunk) * hchunk.size(), sizeof(int32_t) * hwchunk.size(),
+                                  sizeof(uint16_t) * hslot.size()};
     for (int k = 0; k < kParts; ++k) {
         off[k] = total;
         total += align256(sizes[k]);
@@ -739,6 +840,10 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
     d.wsite = balls ? (const int32_t *)(g->mem + off[11]) : nullptr;
     d.la = (const uint16_t *)(g->mem + off[12]);
     d.lb = (const uint16_t *)(g->mem + off[13]);
+    d.dblock = shared ? (const uint32_t *)(g->mem + off[14]) : nullptr;
+    d.dchunk = (const DrawChunk *)(g->mem + off[15]);
+    d.wchunk = (const int32_t *)(g->mem + off[16]);
+    d.dslot = (const uint16_t *)(g->mem + off[17]);
     d.J = J;
     d.key = philox_key(seed);
     graph_params(g, T);
@@ -750,6 +855,16 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
         e = hipMemcpy((void *)d.la, hla.data(), sizeof(uint16_t) * (size_t)n_inside, hipMemcpyHostToDevice);
     if (e == hipSuccess && n_inside > 0)
         e = hipMemcpy((void *)d.lb, hlb.data(), sizeof(uint16_t) * (size_t)n_inside, hipMemcpyHostToDevice);
+    if (shared) {
+        if (e == hipSuccess)
+            e = hipMemcpy((void *)d.dblock, hblock.data(), sizeof(uint32_t) * hblock.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            e = hipMemcpy((void *)d.dchunk, hchunk.data(), sizeof(DrawChunk) * hchunk.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            e = hipMemcpy((void *)d.wchunk, hwchunk.data(), sizeof(int32_t) * hwchunk.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            e = hipMemcpy((void *)d.dslot, hslot.data(), sizeof(uint16_t) * hslot.size(), hipMemcpyHostToDevice);
+    }
     if (n_bonds > 0) {
         if (e == hipSuccess)
             e = hipMemcpy((void *)d.ba, ga.data(), sizeof(int32_t) * (size_t)n_bonds, hipMemcpyHostToDevice);
