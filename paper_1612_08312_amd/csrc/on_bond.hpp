@@ -6,7 +6,9 @@
 // The FP64 log1p is evaluated only when x lies within 1e-4 (1 + t) of
 // t = -ln(1 - u) computed in FP32 with the native base-2 logarithm: that
 // margin exceeds the FP32 error by orders of magnitude, so outside it the
-// FP32 comparison gives the same answer as the exact one.
+// FP32 comparison gives the same answer as the exact one.  1 - u is
+// (not r32 + 0.5) 2^-32: one conversion and one fused multiply-add give it
+// within a relative 2^-23, where five FP64 instructions per bond had.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -26,20 +28,29 @@ __device__ __forceinline__ float project(const float v[NV], const float r[NV])
 
 // The exact comparison, out of line: it is rarely reached, and 48 inlined
 // copies per cell would swell the tile kernel's code.
-static __device__ __noinline__ bool on_bond_exact(float x, double u) { return (double)x > -log1p(-u); }
+static __device__ __noinline__ bool on_bond_exact(float x, uint32_t r32)
+{
+    return (double)x > -log1p(-(((double)r32 + 0.5) * 0x1p-32));
+}
 
-// Exact activation decision of one bond (see the file comment).  1 - u is
-// exact in FP64 and at least 2^-33, so its FP32 rounding is a normal number
-// within a relative 2^-24.
+// FP32 decision of one bond (see the file comment): active, or *close when
+// only the exact comparison can tell.
+__device__ __forceinline__ bool on_bond_filter(float x, uint32_t r32, bool *close)
+{
+    const float v = __fmaf_rn((float)~r32, 0x1p-32f, 0x1p-33f);  // 1 - u, at least 2^-33: a normal number
+    const float t = -0.6931472f * __log2f(v);  // native base-2 logarithm
+    const float m = __fmaf_rn(1e-4f, t, 1e-4f);
+    *close = x > 0.0f && !(x > t + m) && !(x < t - m);
+    return x > t + m;
+}
+
+// Activation of one bond.
 __device__ __forceinline__ bool on_bond_active(float x, uint32_t r32)
 {
     if (!(x > 0.0f)) return false;
-    const double u = ((double)r32 + 0.5) * 0x1p-32;
-    const float t = -0.6931472f * __log2f((float)(1.0 - u));  // native base-2 logarithm
-    const float m = 1e-4f * (1.0f + t);
-    if (x > t + m) return true;
-    if (x < t - m) return false;
-    return on_bond_exact(x, u);
+    bool close;
+    const bool active = on_bond_filter(x, r32, &close);
+    return close ? on_bond_exact(x, r32) : active;
 }
 
 }  // namespace pyro

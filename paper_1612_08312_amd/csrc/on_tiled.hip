@@ -165,20 +165,29 @@ __global__ __launch_bounds__(TX *TY *TZ) __attribute__((amdgpu_waves_per_eu(4)))
                 const float sb = tet < 4 ? sig_own[ib] : sig_dv[ib];
                 xs[k4] = __fmul_rn(__fmul_rn(x0, sa), sb);
                 any |= xs[k4] > 0.0f;
-                double dd = 0.0;
 #pragma unroll
                 for (int k = 0; k < NV; ++k) {
                     const float va = tet < 4 ? own[k][ia] : dv[k][ia];
                     const float vb = tet < 4 ? own[k][ib] : dv[k][ib];
-                    dd += (double)va * (double)vb;
+                    esum = __fma_rn((double)va, (double)vb, esum);
                 }
-                esum += dd;
             }
             if (any) {
                 const uint4 rnd = philox4x32_10(12u * (uint32_t)cell + qg, st.t, kStreamBond, 0u, d.key);
+                // the four filters without a branch; one for the rare close calls
+                uint32_t a4 = 0, c4 = 0;
 #pragma unroll
-                for (int k4 = 0; k4 < 4; ++k4)
-                    if (on_bond_active(xs[k4], word_of(rnd, k4))) act |= 1ull << (4 * qg + k4);
+                for (int k4 = 0; k4 < 4; ++k4) {
+                    bool close;
+                    a4 |= (uint32_t)on_bond_filter(xs[k4], word_of(rnd, k4), &close) << k4;
+                    c4 |= (uint32_t)close << k4;
+                }
+                if (c4) {
+#pragma unroll
+                    for (int k4 = 0; k4 < 4; ++k4)
+                        if (((c4 >> k4) & 1u) && on_bond_exact(xs[k4], word_of(rnd, k4))) a4 |= 1u << k4;
+                }
+                act |= (uint64_t)a4 << (4 * qg);
             }
         }
     }
