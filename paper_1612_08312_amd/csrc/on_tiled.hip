@@ -197,13 +197,13 @@ __global__ __launch_bounds__(TX *TY *TZ) __attribute__((amdgpu_waves_per_eu(4)))
 }
 
 // LDS of the O(n) settle-and-flip pass.
-template <int TX, int TY, int TZ>
+template <int NV, int TX, int TY, int TZ>
 struct OnFlipLds {
     alignas(16) int LAB[16 * TX * TY * TZ];  // labels of the tile's sites
     alignas(16) uint32_t CB[TX * TY * TZ];   // coins of the tile's sites
     uint16_t HL[kSettleListPerCell * TX * TY * TZ];  // local keys of the tile's hooked local roots
     int wtot[TX * TY * TZ / 64];
-    double red[16];
+    double red[16 * NV];
 };
 
 // One workgroup per tile, once every unite is done: the settle step
@@ -212,7 +212,7 @@ struct OnFlipLds {
 // reflections, FP64 magnetisation.
 template <int NV, int TX, int TY, int TZ, int MODE>
 __device__ __forceinline__ void on_settle_flip_pass(const RepDesc &d, const RepState &st, int tile, int tid,
-                                                    OnFlipLds<TX, TY, TZ> &S)
+                                                    OnFlipLds<NV, TX, TY, TZ> &S)
 {
     constexpr int NC = TX * TY * TZ;
     constexpr bool ALIGNED = MODE != kFlipGeneral;  // labels staged by local key, every thread has a cell
@@ -280,17 +280,17 @@ __device__ __forceinline__ void on_settle_flip_pass(const RepDesc &d, const RepS
 #pragma unroll
             for (int q = 0; q < 16; ++q) M[k] += (double)v[k][q];
     }
+    block_sum_n<double, NV>(M, S.red);
+    if (tid == 0) {
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-        const double b = block_sum<double>(M[k], S.red);
-        if (tid == 0) d.dpart[d.mpart_off * (1 + k) + tile] = b;
+        for (int k = 0; k < NV; ++k) d.dpart[d.mpart_off * (1 + k) + tile] = M[k];
     }
 }
 
 template <int NV, int TX, int TY, int TZ>
 __global__ __launch_bounds__(TX *TY *TZ) void k_settle_flip_on(Chain c)
 {
-    __shared__ OnFlipLds<TX, TY, TZ> S;
+    __shared__ OnFlipLds<NV, TX, TY, TZ> S;
     const int rep = c.tile_rep[blockIdx.x];
     const RepState st = c.state[rep][1];
     if (st.remaining <= 0) return;
