@@ -331,12 +331,14 @@ struct IsingFlip {
     }
 };
 
-hipError_t launch_ising_sweep(const Chain &c, hipStream_t st, const LaunchHook &hook)
+hipError_t launch_ising_tiles(const Chain &c, hipStream_t st, const LaunchHook &hook)
 {
-    hipError_t e = with_tile_shape<IsingLocal>(c.shape, c, st, hook);
-    if (e == hipSuccess) e = launch_unite(c, st, hook);
-    if (e == hipSuccess) e = with_tile_shape<IsingFlip>(c.shape, c, st, hook);
-    return e;
+    return with_tile_shape<IsingLocal>(c.shape, c, st, hook);
+}
+
+hipError_t launch_ising_flip(const Chain &c, hipStream_t st, const LaunchHook &hook)
+{
+    return with_tile_shape<IsingFlip>(c.shape, c, st, hook);
 }
 
 hipError_t launch_ising_energy_tail(const Chain &c, hipStream_t st, const LaunchHook &hook)

@@ -133,6 +133,8 @@ struct LaunchHook {
 hipError_t launch_init(const RepDesc &d, int model, int start, hipStream_t st);
 // One sweep of every replica of the chain with remaining > 0.
 hipError_t launch_chain_sweep(const Chain &c, hipStream_t st, const LaunchHook &hook);
+// The same for the chains of a group, at most one a model and in that order.
+hipError_t launch_chains_sweep(const Chain *cs, int n, hipStream_t st);
 // Energy of the current state into the pending record of every replica of
 // the chain, then mark it complete.
 hipError_t launch_chain_energy_tail(const Chain &c, hipStream_t st, const LaunchHook &hook);

@@ -47,21 +47,21 @@ __device__ __forceinline__ void sweep_axis(const RepDesc &d, uint32_t t, float (
 }
 
 
-// Four waves per SIMD, so at most 128 VGPRs: left alone, the Heisenberg pass
-// takes 139 and only three 8x8x4 workgroups share a CU (60 -> 51 us per
-// L = 64 sweep with the cap, despite a few spills).  XY takes 113 either way;
-// a cap of five waves made its pass slower (43 -> 48 us).
+template <int NC>
+struct OnTileLds {
+    uint32_t P[kForestSlots<NC>], U[kUnionWords<NC>], NB[8];
+    uint8_t K4[64];
+    double red[16];
+};
+
+// The tile pass of one tile: block blk of the chain's tile grid.
 template <int NV, int TX, int TY, int TZ>
-__global__ __launch_bounds__(TX *TY *TZ) __attribute__((amdgpu_waves_per_eu(4))) void k_local_on(Chain c)
+__device__ __forceinline__ void on_tile_pass(Chain c, int blk, OnTileLds<TX * TY * TZ> &S)
 {
     constexpr int NC = TX * TY * TZ;
-    __shared__ uint32_t P[kForestSlots<NC>];
-    __shared__ uint32_t U[kUnionWords<NC>];
-    __shared__ uint8_t K4[64];
-    __shared__ uint32_t NB[8];
-    __shared__ double red[16];
-
-    const int blk = blockIdx.x;
+    uint32_t *P = S.P, *U = S.U, *NB = S.NB;
+    uint8_t *K4 = S.K4;
+    double *red = S.red;
     const int rep = c.tile_rep[blk];
     const RepState st = *c.state[rep];
     if (st.remaining <= 0) return;
@@ -196,6 +196,28 @@ __global__ __launch_bounds__(TX *TY *TZ) __attribute__((amdgpu_waves_per_eu(4)))
     if (tid == 0) d.dpart[tile] = b;
 }
 
+// Four waves per SIMD, so at most 128 VGPRs: left alone, the Heisenberg pass
+// takes 139 and only three 8x8x4 workgroups share a CU (60 -> 51 us per
+// L = 64 sweep with the cap, despite a few spills).  XY takes 113 either way;
+// a cap of five waves made its pass slower (43 -> 48 us).
+template <int NV, int TX, int TY, int TZ>
+__global__ __launch_bounds__(TX *TY *TZ) __attribute__((amdgpu_waves_per_eu(4))) void k_local_on(Chain c)
+{
+    __shared__ OnTileLds<TX * TY * TZ> S;
+    on_tile_pass<NV, TX, TY, TZ>(c, blockIdx.x, S);
+}
+
+// The XY and the Heisenberg chain of a mixed group with one tile shape, in
+// one launch (the Heisenberg blocks, the longer ones, first).
+template <int TX, int TY, int TZ>
+__global__ __launch_bounds__(TX *TY *TZ) __attribute__((amdgpu_waves_per_eu(4))) void k_local_on_both(Chain xy, Chain heisenberg)
+{
+    __shared__ OnTileLds<TX * TY * TZ> S;
+    const int blk = (int)blockIdx.x - heisenberg.ntile_blocks;
+    if (blk < 0) on_tile_pass<3, TX, TY, TZ>(heisenberg, blockIdx.x, S);
+    else on_tile_pass<2, TX, TY, TZ>(xy, blk, S);
+}
+
 // LDS of the O(n) settle-and-flip pass.
 template <int NV, int TX, int TY, int TZ>
 struct OnFlipLds {
@@ -288,25 +310,44 @@ __device__ __forceinline__ void on_settle_flip_pass(const RepDesc &d, const RepS
 }
 
 template <int NV, int TX, int TY, int TZ>
-__global__ __launch_bounds__(TX *TY *TZ) void k_settle_flip_on(Chain c)
+__device__ __forceinline__ void on_settle_flip_block(Chain c, int blk, OnFlipLds<NV, TX, TY, TZ> &S)
 {
-    __shared__ OnFlipLds<NV, TX, TY, TZ> S;
-    const int rep = c.tile_rep[blockIdx.x];
+    const int rep = c.tile_rep[blk];
     const RepState st = c.state[rep][1];
     if (st.remaining <= 0) return;
     const RepDesc &d = c.desc[rep];
-    if ((int)blockIdx.x == d.tile_base && threadIdx.x == 0) advance_state(c.state[rep], st, d);
+    if (blk == d.tile_base && threadIdx.x == 0) advance_state(c.state[rep], st, d);
     if constexpr (TX % 8 == 0) {
         if (d.lgL >= 0) {
-            on_settle_flip_pass<NV, TX, TY, TZ, kFlipPow2>(d, st, blockIdx.x - d.tile_base, threadIdx.x, S);
+            on_settle_flip_pass<NV, TX, TY, TZ, kFlipPow2>(d, st, blk - d.tile_base, threadIdx.x, S);
             return;
         }
         if (d.divisible) {
-            on_settle_flip_pass<NV, TX, TY, TZ, kFlipDivisible>(d, st, blockIdx.x - d.tile_base, threadIdx.x, S);
+            on_settle_flip_pass<NV, TX, TY, TZ, kFlipDivisible>(d, st, blk - d.tile_base, threadIdx.x, S);
             return;
         }
     }
-    on_settle_flip_pass<NV, TX, TY, TZ, kFlipGeneral>(d, st, blockIdx.x - d.tile_base, threadIdx.x, S);
+    on_settle_flip_pass<NV, TX, TY, TZ, kFlipGeneral>(d, st, blk - d.tile_base, threadIdx.x, S);
+}
+
+template <int NV, int TX, int TY, int TZ>
+__global__ __launch_bounds__(TX *TY *TZ) void k_settle_flip_on(Chain c)
+{
+    __shared__ OnFlipLds<NV, TX, TY, TZ> S;
+    on_settle_flip_block<NV, TX, TY, TZ>(c, blockIdx.x, S);
+}
+
+// Both O(n) chains of a mixed group, as in the tile pass.
+template <int TX, int TY, int TZ>
+__global__ __launch_bounds__(TX *TY *TZ) void k_settle_flip_on_both(Chain xy, Chain heisenberg)
+{
+    __shared__ union {
+        OnFlipLds<3, TX, TY, TZ> h;
+        OnFlipLds<2, TX, TY, TZ> x;
+    } S;
+    const int blk = (int)blockIdx.x - heisenberg.ntile_blocks;
+    if (blk < 0) on_settle_flip_block<3, TX, TY, TZ>(heisenberg, blockIdx.x, S.h);
+    else on_settle_flip_block<2, TX, TY, TZ>(xy, blk, S.x);
 }
 
 // Energy of the current state for replicas whose last record is pending.
@@ -358,18 +399,43 @@ struct OnFlip {
     }
 };
 
-template <int NV>
-static hipError_t sweep_on(const Chain &c, hipStream_t st, const LaunchHook &hook)
+struct OnLocalBoth {
+    template <int TX, int TY, int TZ>
+    static hipError_t run(const Chain &xy, const Chain &heisenberg, hipStream_t st, const LaunchHook &hook)
+    {
+        PYRO_LAUNCH(kKLocal, (k_local_on_both<TX, TY, TZ>), xy.ntile_blocks + heisenberg.ntile_blocks, TX * TY * TZ, xy, heisenberg);
+        return hipSuccess;
+    }
+};
+
+struct OnFlipBoth {
+    template <int TX, int TY, int TZ>
+    static hipError_t run(const Chain &xy, const Chain &heisenberg, hipStream_t st, const LaunchHook &hook)
+    {
+        PYRO_LAUNCH(kKFlip, (k_settle_flip_on_both<TX, TY, TZ>), xy.ntile_blocks + heisenberg.ntile_blocks, TX * TY * TZ, xy, heisenberg);
+        return hipSuccess;
+    }
+};
+
+hipError_t launch_on_tiles(const Chain &c, hipStream_t st, const LaunchHook &hook)
 {
-    hipError_t e = with_tile_shape<OnLocal<NV>>(c.shape, c, st, hook);
-    if (e == hipSuccess) e = launch_unite(c, st, hook);
-    if (e == hipSuccess) e = with_tile_shape<OnFlip<NV>>(c.shape, c, st, hook);
-    return e;
+    return c.model == 2 ? with_tile_shape<OnLocal<2>>(c.shape, c, st, hook) : with_tile_shape<OnLocal<3>>(c.shape, c, st, hook);
 }
 
-hipError_t launch_on_sweep(const Chain &c, hipStream_t st, const LaunchHook &hook)
+hipError_t launch_on_flip(const Chain &c, hipStream_t st, const LaunchHook &hook)
 {
-    return c.model == 2 ? sweep_on<2>(c, st, hook) : sweep_on<3>(c, st, hook);
+    return c.model == 2 ? with_tile_shape<OnFlip<2>>(c.shape, c, st, hook) : with_tile_shape<OnFlip<3>>(c.shape, c, st, hook);
+}
+
+// The chains have the same tile shape.
+hipError_t launch_on_tiles(const Chain &xy, const Chain &heisenberg, hipStream_t st, const LaunchHook &hook)
+{
+    return with_tile_shape<OnLocalBoth>(xy.shape, xy, heisenberg, st, hook);
+}
+
+hipError_t launch_on_flip(const Chain &xy, const Chain &heisenberg, hipStream_t st, const LaunchHook &hook)
+{
+    return with_tile_shape<OnFlipBoth>(xy.shape, xy, heisenberg, st, hook);
 }
 
 template <int NV>

@@ -601,14 +601,7 @@ hipError_t capture_graph(F launch, hipGraphExec_t *exec)
 // Capture one sweep of the given chains.
 hipError_t capture_sweep(const Chain *chains, int nchains, hipGraphExec_t *exec)
 {
-    const LaunchHook none{nullptr, nullptr, nullptr};
-    return capture_graph(
-        [&](hipStream_t cs) {
-            hipError_t le = hipSuccess;
-            for (int k = 0; k < nchains && le == hipSuccess; ++k) le = launch_chain_sweep(chains[k], cs, none);
-            return le;
-        },
-        exec);
+    return capture_graph([&](hipStream_t cs) { return launch_chains_sweep(chains, nchains, cs); }, exec);
 }
 
 // Arming writes replica states in stream order.  The states travel as

@@ -52,10 +52,69 @@ hipError_t launch_pending_records(const Chain &c, bool with_energy, hipStream_t 
     return hipSuccess;
 }
 
+static hipError_t launch_tiles(const Chain &c, hipStream_t st, const LaunchHook &hook)
+{
+    return c.model == 1 ? launch_ising_tiles(c, st, hook) : launch_on_tiles(c, st, hook);
+}
+
+static hipError_t launch_flip(const Chain &c, hipStream_t st, const LaunchHook &hook)
+{
+    return c.model == 1 ? launch_ising_flip(c, st, hook) : launch_on_flip(c, st, hook);
+}
+
 hipError_t launch_chain_sweep(const Chain &c, hipStream_t st, const LaunchHook &hook)
 {
     if (c.nreps == 0) return hipSuccess;
-    return c.model == 1 ? launch_ising_sweep(c, st, hook) : launch_on_sweep(c, st, hook);
+    hipError_t e = launch_tiles(c, st, hook);
+    if (e == hipSuccess) e = launch_unite(c, st, hook);
+    if (e == hipSuccess) e = launch_flip(c, st, hook);
+    return e;
+}
+
+// The unite pass of two or three chains in one launch: it does not depend on
+// the model or on the tile shape.
+__global__ __launch_bounds__(kUniteThreads) void k_forest_chains(Chain a, Chain b, Chain c)
+{
+    __shared__ UniteLds S;
+    int blk = (int)blockIdx.x;
+    Chain mine = a;
+    if (blk >= a.ntile_blocks + a.nreps) {
+        blk -= a.ntile_blocks + a.nreps;
+        mine = b;
+        if (blk >= b.ntile_blocks + b.nreps) {
+            blk -= b.ntile_blocks + b.nreps;
+            mine = c;
+        }
+    }
+    unite_block<false>(mine, blk, S);
+}
+
+// One sweep of the chains of a group.  Chains of several models share
+// launches: each pass of a chain of a few small lattices leaves most of the
+// chip idle, and the passes of a sweep follow each other.  The unite passes
+// always do; the tile and flip passes of the O(n) chains do when their tile
+// shapes are the same (one launch for two block sizes would leave threads
+// idle).
+hipError_t launch_chains_sweep(const Chain *cs, int n, hipStream_t st)
+{
+    const LaunchHook none{nullptr, nullptr, nullptr};
+    hipError_t e = hipSuccess;
+    if (n < 2 || cs[0].counts) {  // counted unite passes (measurement runs) are launches of their own
+        for (int k = 0; k < n && e == hipSuccess; ++k) e = launch_chain_sweep(cs[k], st, none);
+        return e;
+    }
+    // in the order of the models, so the O(n) chains, if both are there, are the last two
+    const bool both = cs[n - 2].model == 2 && cs[n - 1].model == 3 && cs[n - 2].shape == cs[n - 1].shape;
+    for (int k = 0; k < (both ? n - 2 : n) && e == hipSuccess; ++k) e = launch_tiles(cs[k], st, none);
+    if (both && e == hipSuccess) e = launch_on_tiles(cs[n - 2], cs[n - 1], st, none);
+    if (e != hipSuccess) return e;
+    int grid = 0;
+    for (int k = 0; k < n; ++k) grid += cs[k].ntile_blocks + cs[k].nreps;
+    k_forest_chains<<<grid, kUniteThreads, 0, st>>>(cs[0], cs[1], cs[n - 1]);
+    e = hipGetLastError();
+    for (int k = 0; k < (both ? n - 2 : n) && e == hipSuccess; ++k) e = launch_flip(cs[k], st, none);
+    if (both && e == hipSuccess) e = launch_on_flip(cs[n - 2], cs[n - 1], st, none);
+    return e;
 }
 
 hipError_t launch_chain_energy_tail(const Chain &c, hipStream_t st, const LaunchHook &hook)

@@ -1281,13 +1281,12 @@ __device__ __forceinline__ void write_pending_record(const RepDesc &d, int model
 // counts its compare-and-swaps into c.counts (measurement runs).  The chains
 // settle their roots in the flip pass and run no store pass, so the lists are
 // left as they are.
-template <bool COUNT = false>
-__global__ __launch_bounds__(kUniteThreads) void k_forest(Chain c)
+template <bool COUNT>
+__device__ __forceinline__ void unite_block(Chain c, uint32_t b, UniteLds &S)
 {
     static_assert(kUniteThreads == kBlock, "the record block");
-    __shared__ UniteLds S;
-    if ((int)blockIdx.x >= c.ntile_blocks) {
-        const int rep = (int)blockIdx.x - c.ntile_blocks;
+    if ((int)b >= c.ntile_blocks) {
+        const int rep = (int)b - c.ntile_blocks;
         const RepDesc &d = c.desc[rep];
         const RepState st = c.state[rep][0];
         if (threadIdx.x == 0) c.state[rep][1] = st;
@@ -1296,11 +1295,18 @@ __global__ __launch_bounds__(kUniteThreads) void k_forest(Chain c)
                                  S.BEST);
         return;
     }
-    const int blk = xcd_block(blockIdx.x, c.ntile_blocks);
+    const int blk = xcd_block(b, c.ntile_blocks);
     const int rep = c.tile_rep[blk];
     if (c.state[rep]->remaining <= 0) return;
     const RepDesc &d = c.desc[rep];
     unite_tile<kUniteThreads, COUNT>(d, blk - d.tile_base, threadIdx.x, S, c.counts, false);
+}
+
+template <bool COUNT = false>
+__global__ __launch_bounds__(kUniteThreads) void k_forest(Chain c)
+{
+    __shared__ UniteLds S;
+    unite_block<COUNT>(c, blockIdx.x, S);
 }
 
 // First block of a replica in the settle-and-flip pass: the state of the next
@@ -1329,9 +1335,13 @@ hipError_t launch_unite(const Chain &c, hipStream_t st, const LaunchHook &hook);
 hipError_t launch_pending_records(const Chain &c, bool with_energy, hipStream_t st, const LaunchHook &hook);
 
 // Per-model chain launchers (ising_tiled.hip, on_tiled.hip).
-hipError_t launch_ising_sweep(const Chain &c, hipStream_t st, const LaunchHook &hook);
+hipError_t launch_ising_tiles(const Chain &c, hipStream_t st, const LaunchHook &hook);
+hipError_t launch_ising_flip(const Chain &c, hipStream_t st, const LaunchHook &hook);
 hipError_t launch_ising_energy_tail(const Chain &c, hipStream_t st, const LaunchHook &hook);
-hipError_t launch_on_sweep(const Chain &c, hipStream_t st, const LaunchHook &hook);
+hipError_t launch_on_tiles(const Chain &c, hipStream_t st, const LaunchHook &hook);
+hipError_t launch_on_flip(const Chain &c, hipStream_t st, const LaunchHook &hook);
+hipError_t launch_on_tiles(const Chain &xy, const Chain &heisenberg, hipStream_t st, const LaunchHook &hook);
+hipError_t launch_on_flip(const Chain &xy, const Chain &heisenberg, hipStream_t st, const LaunchHook &hook);
 hipError_t launch_on_energy_tail(const Chain &c, hipStream_t st, const LaunchHook &hook);
 
 }  // namespace pyro
