@@ -193,6 +193,10 @@ int admit(pyro_sw_server *s, bool *progress)
             head = false;
             continue;
         }
+        // A lane's stream is made when its first job comes: a process has four
+        // hardware queues, and two lanes on one queue do not overlap.
+        if (!ln.st && hipStreamCreateWithFlags(&ln.st, hipStreamNonBlocking) != hipSuccess)
+            return server_fail(s, PYRO_EDEVICE, "lane stream creation failed");
         pyro_sw *h = nullptr;
         const int rc = pyro_sw_init_ext(&h, j->spec.L, j->spec.model, j->spec.T, j->spec.J, j->spec.seed,
                                         j->spec.start, ln.st, s->base + off, j->spin_bytes,
@@ -305,10 +309,9 @@ int pyro_sw_server_create(pyro_sw_server **out, size_t hbm_budget, int max_runni
     }
     s->arena = Arena(budget, kAlign);
     for (Lane &ln : s->lanes) {
-        if (hipStreamCreateWithFlags(&ln.st, hipStreamNonBlocking) != hipSuccess ||
-            hipEventCreate(&ln.e0) != hipSuccess || hipEventCreate(&ln.e1) != hipSuccess) {
+        if (hipEventCreate(&ln.e0) != hipSuccess || hipEventCreate(&ln.e1) != hipSuccess) {
             pyro_sw_server_destroy(s);
-            return record_error(PYRO_EDEVICE, "lane stream or event creation failed");
+            return record_error(PYRO_EDEVICE, "lane event creation failed");
         }
     }
     *out = s;
