@@ -111,9 +111,11 @@ int pyro_sw_init_ext(pyro_sw **out, int L, int model, double T, double J, uint64
 /*
  * Enqueue n_sweeps >= 0 Swendsen-Wang sweeps (bond activation, cluster
  * labeling, cluster flips, moments).  Asynchronous on the handle's stream
- * (one captured graph replayed per sweep); records are kept on the device and
- * drained to the host automatically when the device ring of 16384 records
- * fills (which synchronises).  Errors: PYRO_EINVAL (n_sweeps < 0),
+ * (one captured graph replayed per sweep; Ising lattices without vacant sites
+ * of L <= 12, and of L = 13 from four sweeps a call on, run every sweep of a
+ * call in one launch, held in LDS); records are kept on the device and drained
+ * to the host automatically when the device ring of 16384 records fills (which
+ * synchronises).  Errors: PYRO_EINVAL (n_sweeps < 0),
  * PYRO_EDEVICE, PYRO_ESTATE.
  */
 int pyro_sw_sweep(pyro_sw *h, int64_t n_sweeps);
@@ -390,7 +392,10 @@ int pyro_sw_atomic_rate(int mode, int64_t words, int64_t ops, int repeats, doubl
  *                          model, T, J, seed, start and stream as in
  *                          pyro_sw_init.  One device allocation: 12 B per
  *                          bond (ends and table position) and 4 B more per
- *                          bond inside a 4096-site window, spins, 4 B per
+ *                          bond inside a window (512 to 4096 sites, by
+ *                          n_sites; Ising: 2 B more, and 4 B per distinct
+ *                          random block of a window's bonds, when a block
+ *                          serves two bonds or more), spins, 4 B per
  *                          site of labels (O(n): 4 more of projections; 4
  *                          more for the window site lists when the windows
  *                          are breadth-first balls), partials, a record

@@ -644,11 +644,19 @@ LaunchHook hook_of(Timer &tm, hipStream_t st)
 // Resident against tiled, us per sweep of a long call: L = 4 5.7 / 31, L = 8
 // 11 / 43, L = 12 34 / 53, L = 13 43 / 53.  Setting up costs a call of one
 // sweep more than it gains only beyond L = 12 (L = 13 with its record read:
-// 108 / 106 us).
+// 108 / 106 us).  A stream that is being captured takes the graph path, which
+// decides what the runtime makes of it.
 bool solo_resident(const pyro_sw *h, int64_t n)
 {
-    return h->model == PYRO_ISING && (h->L <= 12 || (h->L <= kQuadMaxL && n >= 4)) && !h->diluted && !h->shape_chosen &&
-           h->timer.mask == 0;
+    if (h->model != PYRO_ISING || (h->L > 12 && (h->L > kQuadMaxL || n < 4)) || h->diluted || h->shape_chosen ||
+        h->timer.mask != 0)
+        return false;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return capture == hipStreamCaptureStatusNone;
 }
 
 // Energy of the pending record (tail), then copy the ring to the host queue.

@@ -39,7 +39,7 @@ __host__ __device__ inline ResidentLayout resident_layout(int L)
 // sums (three sets of two words: magnetisation, aligned bonds), number of
 // tied bonds, K4 table, coin words (whole FLIP blocks), union buffers (128
 // words per wave), tied bonds (two words each), cell spin masks.  At L = 13:
-// 161,912 B.
+// 161,788 B.
 constexpr int kQuadTies = 512;
 struct QuadLayout {
     uint32_t p, sums, ties_n, k4, cw, un, ties, smk, total;
