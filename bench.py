@@ -465,8 +465,8 @@ def kernel_bounds(kt, N, cas_per_launch, hooks_per_launch, cas_ceiling, copy_gbs
     its settle walks; the
     unite pass by device atomics
     (compare-and-swaps per launch / duration, against the measured random
-    compare-and-swap rate); the finalize by launch latency (one workgroup
-    per lattice).  There is no store pass: each tile settles its own hooked
+    compare-and-swap rate); the finalize (at drains only: the unite
+    pass writes the records) by launch latency (one workgroup per lattice).  There is no store pass: each tile settles its own hooked
     roots at the start of its flip."""
     out = {}
     for k, (n, ms) in kt.items():
