@@ -214,7 +214,8 @@ int pyro_sw_kernel_times(pyro_sw *h, const char **names, int64_t *launches, doub
  *                          stream on every call, so that the latency-bound
  *                          passes of one slice overlap the arithmetic of
  *                          another (members are dealt largest first to the
- *                          lightest slice; default min(n, 2)).  Changes speed
+ *                          lightest slice; default 1, and min(n, 2) from
+ *                          6 million sites on).  Changes speed
  *                          only, never results.
  *   pyro_sw_group_set_mode how the Ising members are swept (the O(n)
  *                          members always use per-sweep graphs):

@@ -115,7 +115,13 @@ constexpr int kMaxSlices = 8;  // concurrent slices of a group
 // 1 / 2 / 4 / 8 slices: five L = 128 lattices (five at most) 1.33 / 1.33 /
 // 1.34 / 1.34 ms, 48 Ising replicas of L = 8 to 48 460 / 446 / 486 / 527 us,
 // 27 Heisenberg lattices of L = 24 to 48 633 / 609 / 609 / 599 us.
+// A group of few sites runs in one: its launches leave the chip idle as they
+// are, and a second stream doubles them.  With 1 / 2 slices: two Ising lattices
+// of L = 48 (3.5 M sites) 79 / 87 us, two of L = 64 (8.4 M) 119 / 112 us; XY
+// 93 / 98 and 150 / 144 us, Heisenberg 103 / 108 and 172 / 164 us; two of
+// L = 12 54 / 72 us.
 constexpr int kDefaultSlices = 2;
+constexpr int64_t kTwoSliceSites = 6000000;
 constexpr size_t kAlign = 256;
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -1332,7 +1338,9 @@ int pyro_sw_group_create(pyro_sw_group **out, pyro_sw *const *members, int n, vo
             g->resident = it->second.resident;
         }
     }
-    if (int rc = make_slices(g, std::min(n, kDefaultSlices))) {
+    int64_t sites = 0;
+    for (const pyro_sw *h : g->members) sites += h->N;
+    if (int rc = make_slices(g, sites < kTwoSliceSites ? 1 : std::min(n, kDefaultSlices))) {
         pyro_sw_group_destroy(g);
         return rc;
     }
