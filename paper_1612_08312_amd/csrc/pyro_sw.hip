@@ -750,7 +750,8 @@ int create(pyro_sw **out, int L, int model, double T, double J, uint64_t seed, i
     hipError_t e = hipStreamSynchronize(h->stream);
     if (e == hipSuccess)
         e = hipMemcpy(h->work + ly.solo_map, zeros.data(), sizeof(int) * zeros.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(h->d_state, &h->hs, sizeof(RepState), hipMemcpyHostToDevice);
+    const RepState states[kStateSlots] = {h->hs, h->hs, RepState{}};  // both states; no partials yet
+    if (e == hipSuccess) e = hipMemcpy(h->d_state, states, sizeof(states), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = build_solo_chain(h);
     if (e == hipSuccess) e = launch_init(make_desc(h, h->solo_shape, 0, 0), model, start, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
@@ -1151,7 +1152,7 @@ int static_scratch(char **out)
     return PYRO_OK;
 }
 
-// Descriptor, state and zero block map of a solo chain written into the
+// Descriptor, states and zero block map of a solo chain written into the
 // scratch by one kernel whose arguments carry them (no host buffer, no
 // memset node).
 __global__ void k_static_setup(RepDesc *desc_dst, RepDesc d, RepState **stp_dst, RepState *state, RepState s,
@@ -1161,7 +1162,8 @@ __global__ void k_static_setup(RepDesc *desc_dst, RepDesc d, RepState **stp_dst,
     if (i == 0) {
         *desc_dst = d;
         *stp_dst = state;
-        *state = s;
+        state[0] = state[1] = s;
+        mag_partials(state) = 0;
     }
     for (int k = i; k < map_len; k += gridDim.x * blockDim.x) map[k] = 0;
 }
@@ -1532,7 +1534,10 @@ int pyro_sw_group_sweep(pyro_sw_group *g, int64_t n_sweeps, const int64_t *per_m
             if (k > 0) {
                 h->hs.t += (uint32_t)k;
                 h->hs.ring_used += (int32_t)k;
-                h->hs.e_pending = h->hs.ring_used - 1;
+                // An LDS-resident launch completes every record itself and
+                // leaves no partials, from which a later tiled sweep would
+                // write the record again.
+                h->hs.e_pending = resident_member(g, h) ? -1 : h->hs.ring_used - 1;
             }
             h->hs.remaining = 0;
             want[i] -= k;
