@@ -6,7 +6,9 @@
 // per site.  Per sweep:
 //              k_graph_local      sites cut into windows, one workgroup each:
 //                                 O(n) sigma_i = s_i . r (each lane draws the
-//                                 sweep's embedding axis r itself); activation
+//                                 sweep's embedding axis r itself; a pass
+//                                 before it, k_graph_project, for large tables
+//                                 with scattered windows); activation
 //                                 of the bonds with both ends in the window
 //                                 and their union in LDS; every site stores
 //                                 its local root
@@ -83,6 +85,7 @@ struct GraphDesc {
     void *spins;  // int8 [N] or float [n][N]
     int32_t *label;
     float *sigma;  // O(n) projections [N]
+    bool project_first;  // O(n): written by a pass of their own (project_in_order)
     int64_t *ipart;  // Ising partials: [kPartBlocks bond blocks][kPartBlocks site blocks]
     double *dpart;   // O(n) partials: [kPartBlocks bond blocks][3][kPartBlocks site blocks]
     DevRecord *ring;
@@ -158,6 +161,19 @@ __device__ __forceinline__ void graph_axis(const GraphDesc &g, uint32_t t, float
 {
     if (threadIdx.x == 0) unit_vector(0u, t, kStreamAxis, g.n, g.key, ax);
     __syncthreads();
+}
+
+// Projections of all sites, in the order of their indices.
+__global__ __launch_bounds__(kBlock) void k_graph_project(GraphDesc g, uint32_t t)
+{
+    __shared__ float ax[3];
+    graph_axis(g, t, ax);
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= g.N) return;
+    const float *s = (const float *)g.spins;
+    const float r[3] = {ax[0], ax[1], ax[2]};
+    const float v[3] = {s[i], s[g.N + i], g.n == 3 ? s[2 * g.N + i] : 0.0f};
+    g.sigma[i] = g.n == 2 ? project<2>(v, r) : project<3>(v, r);
 }
 
 // Low draw of bond b, whose top byte ties, in sweep t.
@@ -246,11 +262,11 @@ __device__ __forceinline__ void lds_link(int *P, int a, int b)
 // One workgroup per window: union of the active bonds with both ends in the
 // window in LDS, then every site of the window stores the global index of its
 // local root.  O(n): the projections of the window's sites on the sweep's axis
-// first, kept for the later passes.  Shared draws (Ising): the window's
+// first, kept for the later passes (kProjected: read).  Shared draws (Ising): the window's
 // Philox blocks are drawn once each into LDS, a chunk at a time, and a bond
 // reads its byte; drawn per bond, 16 bonds of a block made the pass spend two
 // thirds of its instructions on them.
-template <int kWindow, bool kShared>
+template <int kWindow, bool kShared, bool kProjected = false>
 __global__ __launch_bounds__(kLocalThreads) void k_graph_local(GraphDesc g, uint32_t t)
 {
     __shared__ int P[kWindow];
@@ -262,12 +278,14 @@ __global__ __launch_bounds__(kLocalThreads) void k_graph_local(GraphDesc g, uint
     const int nloc = (int)std::min<int64_t>(kWindow, g.N - base);
     const int32_t *ws = g.wsite ? g.wsite + base : nullptr;  // uniform
     float r[3] = {0.0f, 0.0f, 0.0f};
-    if (!kShared && g.n > 1) unit_vector(0u, t, kStreamAxis, g.n, g.key, r);  // the same in every lane
+    if (!kShared && !kProjected && g.n > 1) unit_vector(0u, t, kStreamAxis, g.n, g.key, r);  // the same in every lane
     for (int k = threadIdx.x; k < nloc; k += kLocalThreads) {
         const int64_t i = ws ? (int64_t)ws[k] : base + k;
         P[k] = k;
         if (kShared) {
             SP[k] = ((const int8_t *)g.spins)[i];
+        } else if (kProjected) {
+            SG[k] = g.sigma[i];
         } else if (g.n == 1) {
             SG[k] = (float)((const int8_t *)g.spins)[i];
         } else {
@@ -334,6 +352,13 @@ template <int kWindow>
 void launch_graph_local(const GraphDesc &g, uint32_t t, hipStream_t st)
 {
     const int nwin = blocks_for(g.N, kWindow);
+    if constexpr (kWindow >= 2048) {  // no smaller table takes the pass of projections
+        if (g.project_first) {
+            k_graph_project<<<blocks_for(g.N), kBlock, 0, st>>>(g, t);
+            k_graph_local<kWindow, false, true><<<nwin, kLocalThreads, 0, st>>>(g, t);
+            return;
+        }
+    }
     if (g.dblock) k_graph_local<kWindow, true><<<nwin, kLocalThreads, 0, st>>>(g, t);
     else k_graph_local<kWindow, false><<<nwin, kLocalThreads, 0, st>>>(g, t);
 }
@@ -675,6 +700,23 @@ void graph_windows(int64_t N, int64_t NB, int kWindow, const int32_t *ba, const 
     wsite.swap(order);
 }
 
+// Do the projections of an O(n) graph take a pass of their own, in the order
+// of the site indices, instead of the window pass?  The window pass reads the
+// n spin components and writes the projections in the order of its sites: a
+// launch less, but scattered words when neighbouring indices seldom share a
+// window (mean run of consecutive indices in the windows' lists below 2, as in
+// random graphs).  Own pass / window pass, us per sweep of random graphs of
+// degree 4 at high temperature: Heisenberg 2 M sites 483 / 541, 600,000 115 /
+// 122, 100,000 40.3 / 38.9; XY 369 / 402, 99.5 / 103, 40.8 / 39.9; simple cubic
+// L = 64 (runs of 5) XY 47.3 / 45.6.
+bool project_in_order(const std::vector<int32_t> &wsite)
+{
+    if (wsite.size() < ((size_t)1 << 19)) return false;
+    size_t runs = 1;
+    for (size_t q = 1; q < wsite.size(); ++q) runs += wsite[q] != wsite[q - 1] + 1;
+    return wsite.size() < 2 * runs;
+}
+
 }  // namespace
 
 extern "C" {
@@ -844,6 +886,7 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
     d.dchunk = (const DrawChunk *)(g->mem + off[15]);
     d.wchunk = (const int32_t *)(g->mem + off[16]);
     d.dslot = (const uint16_t *)(g->mem + off[17]);
+    d.project_first = model != PYRO_ISING && project_in_order(wsite);
     d.J = J;
     d.key = philox_key(seed);
     graph_params(g, T);
