@@ -43,6 +43,7 @@
 
 #include "../../include/pyro_sw.h"
 #include "device_util.hpp"
+#include "graph_draws.hpp"
 #include "kernels.hpp"
 #include "lattice.hpp"
 #include "on_bond.hpp"
@@ -56,11 +57,6 @@ constexpr int kGraphRing = 1024;  // device records between drains
 // One word for all blocks of the union passes serialised their additions.
 constexpr int kAccLines = 64, kAccStride = 16;  // words (128 bytes) apart
 
-constexpr int kDrawChunk = 1024;  // Philox blocks a window pass keeps in LDS at a time
-struct DrawChunk {
-    int64_t bond, block;
-};
-
 struct GraphDesc {
     int64_t N, NB;
     int64_t n_cross;  // bonds between windows (the last n_cross of the bond arrays)
@@ -73,13 +69,10 @@ struct GraphDesc {
     const int32_t *wsite;    // [N] window w holds the sites wsite[w window ..], ascending within the
                              // window; NULL: window w holds the indices w window ..
     const uint16_t *la, *lb; // bonds inside a window: positions of their ends in the window
-    // Ising with shared draws (dblock not NULL): the distinct Philox blocks of
-    // each window's bonds, cut into chunks of kDrawChunk; chunk k of the graph
-    // holds the blocks from dchunk[k].block and the bonds from dchunk[k].bond
-    // on, window w the chunks from wchunk[w] on, and dslot is each inside
-    // bond's byte in its chunk
+    // Ising with shared draws (dblock not NULL): block, chunk, wchunk and slot
+    // of DrawTables
     const uint32_t *dblock;
-    const struct DrawChunk *dchunk;
+    const DrawChunk *dchunk;
     const int32_t *wchunk;
     const uint16_t *dslot;
     void *spins;  // int8 [N] or float [n][N]
@@ -763,16 +756,23 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
     const bool balls = !wsite.empty();
     auto wof = [&](int32_t i) -> int64_t { return balls ? (int64_t)win[(size_t)i] : (int64_t)(i / kWindow); };
     auto pof = [&](int32_t i) -> uint16_t { return balls ? pos[(size_t)i] : (uint16_t)(i % kWindow); };
-    std::vector<int64_t> wstart((size_t)nwin + 1, 0);
-    std::vector<int32_t> ga((size_t)n_bonds), gb((size_t)n_bonds);
-    std::vector<uint32_t> gid((size_t)n_bonds);
-    auto inside = [&](int64_t k) { return wof(bond_a[k]) == wof(bond_b[k]); };
-    for (int64_t k = 0; k < n_bonds; ++k)
-        if (inside(k)) ++wstart[(size_t)wof(bond_a[k]) + 1];
-    for (int64_t w = 0; w < nwin; ++w) wstart[(size_t)w + 1] += wstart[(size_t)w];
-    const int64_t n_inside = wstart[(size_t)nwin];
-    std::vector<uint16_t> hla((size_t)n_inside), hlb((size_t)n_inside);
-    {
+    std::vector<int64_t> wstart;
+    std::vector<int32_t> ga, gb;
+    std::vector<uint32_t> gid;
+    std::vector<uint16_t> hla, hlb;
+    int64_t n_inside = 0;
+    try {
+        wstart.assign((size_t)nwin + 1, 0);
+        ga.resize((size_t)n_bonds);
+        gb.resize((size_t)n_bonds);
+        gid.resize((size_t)n_bonds);
+        auto inside = [&](int64_t k) { return wof(bond_a[k]) == wof(bond_b[k]); };
+        for (int64_t k = 0; k < n_bonds; ++k)
+            if (inside(k)) ++wstart[(size_t)wof(bond_a[k]) + 1];
+        for (int64_t w = 0; w < nwin; ++w) wstart[(size_t)w + 1] += wstart[(size_t)w];
+        n_inside = wstart[(size_t)nwin];
+        hla.resize((size_t)n_inside);
+        hlb.resize((size_t)n_inside);
         std::vector<int64_t> cur(wstart.begin(), wstart.end() - 1);
         int64_t cross = n_inside;
         for (int64_t k = 0; k < n_bonds; ++k) {
@@ -786,50 +786,16 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
                 hlb[(size_t)q] = pof(bond_b[k]);
             }
         }
+    } catch (const std::bad_alloc &) {
+        delete g;
+        return gfail(PYRO_ENOMEM, "graph host memory");
     }
     win.clear();
     win.shrink_to_fit();
     pos.clear();
     pos.shrink_to_fit();
-    // Shared draws: a window's inside bonds are in table order, so the bonds
-    // of a Philox block (16 consecutive positions) follow one another.  Used
-    // where a block serves two of a window's bonds or more on average (a
-    // lattice numbered row by row: 8 or more), else each bond draws its own.
-    std::vector<uint32_t> hblock;
-    std::vector<DrawChunk> hchunk;
-    std::vector<int32_t> hwchunk;
-    std::vector<uint16_t> hslot;
-    if (model == PYRO_ISING && n_inside > 0) {
-        hslot.resize((size_t)n_inside);
-        hwchunk.resize((size_t)nwin + 1);
-        for (int64_t w = 0; w < nwin; ++w) {
-            hwchunk[(size_t)w] = (int32_t)hchunk.size();
-            int fill = kDrawChunk;  // blocks in the open chunk
-            uint32_t last = 0;
-            for (int64_t q = wstart[(size_t)w]; q < wstart[(size_t)w + 1]; ++q) {
-                const uint32_t blk = gid[(size_t)q] >> 4;
-                if (q == wstart[(size_t)w] || blk != last) {
-                    if (fill == kDrawChunk) {
-                        hchunk.push_back({q, (int64_t)hblock.size()});
-                        fill = 0;
-                    }
-                    hblock.push_back(blk);
-                    ++fill;
-                    last = blk;
-                }
-                hslot[(size_t)q] = (uint16_t)(16 * (fill - 1) + (int)(gid[(size_t)q] & 15u));
-            }
-        }
-        hwchunk[(size_t)nwin] = (int32_t)hchunk.size();
-        hchunk.push_back({n_inside, (int64_t)hblock.size()});
-    }
-    const bool shared = !hblock.empty() && 2 * (int64_t)hblock.size() <= n_inside;
-    if (!shared) {
-        hblock.clear();
-        hchunk.clear();
-        hwchunk.clear();
-        hslot.clear();
-    }
+    const DrawTables draws = model == PYRO_ISING ? draw_tables(wstart, gid) : DrawTables();
+    const bool shared = draws.shared();
     constexpr int kParts = 18;
     size_t off[kParts], total = 0;
     const size_t sizes[kParts] = {sizeof(int32_t) * (size_t)n_bonds, sizeof(int32_t) * (size_t)n_bonds, spin_bytes,
@@ -838,9 +804,9 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
                                   sizeof(DevRecord) * (kGraphRing + 1), sizeof(uint32_t) * (size_t)n_bonds,
                                   sizeof(int64_t) * (size_t)(nwin + 1), sizeof(unsigned long long) * kAccLines * kAccStride,
                                   sizeof(int32_t) * wsite.size(), sizeof(uint16_t) * (size_t)n_inside,
-                                  sizeof(uint16_t) * (size_t)n_inside, sizeof(uint32_t) * hblock.size(),
-                                  sizeof(DrawChunk) * hchunk.size(), sizeof(int32_t) * hwchunk.size(),
-                                  sizeof(uint16_t) * hslot.size()};
+                                  sizeof(uint16_t) * (size_t)n_inside, sizeof(uint32_t) * draws.block.size(),
+                                  sizeof(DrawChunk) * draws.chunk.size(), sizeof(int32_t) * draws.wchunk.size(),
+                                  sizeof(uint16_t) * draws.slot.size()};
     for (int k = 0; k < kParts; ++k) {
         off[k] = total;
         total += align256(sizes[k]);
@@ -900,13 +866,13 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
         e = hipMemcpy((void *)d.lb, hlb.data(), sizeof(uint16_t) * (size_t)n_inside, hipMemcpyHostToDevice);
     if (shared) {
         if (e == hipSuccess)
-            e = hipMemcpy((void *)d.dblock, hblock.data(), sizeof(uint32_t) * hblock.size(), hipMemcpyHostToDevice);
+            e = hipMemcpy((void *)d.dblock, draws.block.data(), sizeof(uint32_t) * draws.block.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess)
-            e = hipMemcpy((void *)d.dchunk, hchunk.data(), sizeof(DrawChunk) * hchunk.size(), hipMemcpyHostToDevice);
+            e = hipMemcpy((void *)d.dchunk, draws.chunk.data(), sizeof(DrawChunk) * draws.chunk.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess)
-            e = hipMemcpy((void *)d.wchunk, hwchunk.data(), sizeof(int32_t) * hwchunk.size(), hipMemcpyHostToDevice);
+            e = hipMemcpy((void *)d.wchunk, draws.wchunk.data(), sizeof(int32_t) * draws.wchunk.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess)
-            e = hipMemcpy((void *)d.dslot, hslot.data(), sizeof(uint16_t) * hslot.size(), hipMemcpyHostToDevice);
+            e = hipMemcpy((void *)d.dslot, draws.slot.data(), sizeof(uint16_t) * draws.slot.size(), hipMemcpyHostToDevice);
     }
     if (n_bonds > 0) {
         if (e == hipSuccess)
