@@ -224,6 +224,24 @@ constexpr int kLocalThreads = 512;  // threads of the window pass
 // pass has a workgroup for most compute units.
 inline int window_of(int64_t n) { return n >= (1 << 20) ? 4096 : n >= (1 << 19) ? 2048 : n >= (1 << 17) ? 1024 : 512; }
 
+// One window for a whole graph of few sites and bonds, of whose n_bonds
+// windows of 512 cut n_cut: the pass over the cut bonds and its walks then
+// cost more than the one workgroup.  Us per sweep of an Ising graph with
+// windows of 512 / one window, far below its ordering temperature and above:
+// random, 1000 sites, 3000 bonds 30.1 / 18.8 and 21.6 / 16.4, 8000 bonds 46.9 /
+// 29.9 and 22.2 / 20.7; 1700 sites, 6800 bonds 41.9 / 28.2 and 22.4 / 21.5,
+// 10,200 bonds 51.9 / 36.2 and 23.3 / 25.0; 2300 sites, 4600 bonds 33.4 / 25.6
+// and 22.6 / 19.9; 4000 sites, 8000 bonds 32.6 / 36.2 and 24.3 / 26.3; simple
+// cubic L = 10 23.1 / 20.8 and 18.4 / 16.4.  Not where few bonds are cut, since
+// one window's trees then only grow deeper: rings of 1000 sites 43 / 69 and
+// 15.3 / 12.2, square L = 40 28.8 / 44.5 and 18.3 / 16.7.
+inline bool one_window(int64_t n, int64_t n_bonds, int64_t n_cut)
+{
+    if (n > 4096) return false;
+    const int64_t most = n <= 1024 ? 8192 : n <= 2048 ? 7168 : 5120;
+    return n_bonds <= most && n_cut * (n <= 1024 ? 50 : 4) >= n_bonds;
+}
+
 __device__ __forceinline__ int lds_root(const int *P, int x)
 {
     for (;;) {
@@ -742,8 +760,7 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
     // sort), then the bonds between windows in table order; bond_id keeps
     // each one's position in the caller's table, and la / lb the positions of
     // an inside bond's ends in its window.
-    const int kWindow = window_of(n_sites);
-    const int64_t nwin = (n_sites + kWindow - 1) / kWindow;
+    int kWindow = window_of(n_sites);
     std::vector<int32_t> wsite, win;
     std::vector<uint16_t> pos;
     try {
@@ -753,9 +770,19 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
         win.clear();
         pos.clear();
     }
-    const bool balls = !wsite.empty();
+    bool balls = !wsite.empty();
     auto wof = [&](int32_t i) -> int64_t { return balls ? (int64_t)win[(size_t)i] : (int64_t)(i / kWindow); };
     auto pof = [&](int32_t i) -> uint16_t { return balls ? pos[(size_t)i] : (uint16_t)(i % kWindow); };
+    if (n_sites > kWindow && n_sites <= 4096) {
+        int64_t cut = 0;
+        for (int64_t k = 0; k < n_bonds; ++k) cut += wof(bond_a[k]) != wof(bond_b[k]);
+        if (one_window(n_sites, n_bonds, cut)) {
+            while (kWindow < n_sites) kWindow *= 2;
+            balls = false;
+            wsite.clear();
+        }
+    }
+    const int64_t nwin = (n_sites + kWindow - 1) / kWindow;
     std::vector<int64_t> wstart;
     std::vector<int32_t> ga, gb;
     std::vector<uint32_t> gid;

@@ -39,3 +39,19 @@ def test_projections_in_site_order(n, model, T):
     """Random tables from 2^19 sites on write the projections in a pass of
     their own."""
     check(random_table(n, 2 * n), n, model, T, 4)
+
+
+def ring(n):
+    i = np.arange(n, dtype=np.int32)
+    return i, ((i + 1) % n).astype(np.int32)
+
+
+# One window for a small graph of few bonds, most of them cut, else windows of
+# 512 sites: at most 8192 bonds up to 1024 sites, 7168 up to 2048, 5120 up to
+# 4096.  (sites, bonds; None: a ring, which windows of 512 hardly cut)
+@pytest.mark.parametrize("model", [1, 2])
+@pytest.mark.parametrize("n,bonds", [(513, 900), (1024, 8192), (1024, 8193), (1025, 7168), (2048, 7169), (2049, 5120),
+                                     (4096, 5120), (4096, 5121), (4097, 3000), (600, None), (3000, None)])
+def test_small_tables_of_one_window_or_several(n, bonds, model):
+    table = ring(n) if bonds is None else random_table(n, bonds, n)
+    check(table, n, model, 2.0 * len(table[0]) / n / (1 if model == 1 else 3), 25)
