@@ -54,7 +54,9 @@ namespace pyro {
 namespace {
 
 constexpr int kGraphRing = 1024;  // device records between drains
-// One word for all blocks of the union passes serialised their additions.
+// One word for all blocks of the union passes serialised their additions.  A
+// graph of one window has one block to add: it keeps one word, since reading
+// 64 costs the finalize 0.6 us of the 10 us that its sweep takes.
 constexpr int kAccLines = 64, kAccStride = 16;  // words (128 bytes) apart
 
 struct GraphDesc {
@@ -83,8 +85,9 @@ struct GraphDesc {
     double *dpart;   // O(n) partials: [kPartBlocks bond blocks][3][kPartBlocks site blocks]
     DevRecord *ring;
     unsigned long long *eacc;  // Ising: bond sum of the state entering the sweep, summed by the union
-                               // passes into kAccLines words of a line each; the finalize moves their
+                               // passes into acc_lines words of a line each; the finalize moves their
                                // sum into the record and clears them
+    int acc_lines;             // kAccLines, or 1
     uint32_t thr_hi, thr_lo;  // Ising threshold split at bit 24
     float x0;
     double J;
@@ -211,7 +214,8 @@ __device__ __forceinline__ void add_bond_sum(const GraphDesc &g, int64_t e, int6
     if (g.n != 1) return;
     const int64_t bs = block_sum<int64_t>(e, red);
     if (threadIdx.x == 0 && bs != 0)
-        __hip_atomic_fetch_add(g.eacc + kAccStride * (blockIdx.x % kAccLines), (unsigned long long)bs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(g.eacc + kAccStride * (blockIdx.x % (unsigned)g.acc_lines), (unsigned long long)bs,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Sites are cut into windows of g.window sites (the last may hold fewer):
@@ -482,11 +486,11 @@ __global__ __launch_bounds__(kBlock) void k_graph_finalize(GraphDesc g, uint32_t
         for (int k = threadIdx.x; k < nsp; k += kBlock) M += g.ipart[kPartBlocks + k];
         M = block_sum<int64_t>(M, ired);
         int64_t B = 0;
-        if (threadIdx.x < kAccLines) {
+        if (threadIdx.x < g.acc_lines) {
             B = (int64_t)g.eacc[kAccStride * threadIdx.x];
             g.eacc[kAccStride * threadIdx.x] = 0ull;
         }
-        B = block_sum<int64_t>(B, ired);
+        if (g.acc_lines > 1) B = block_sum<int64_t>(B, ired);  // uniform
         if (threadIdx.x == 0) {
             r.reserved = B;
             r.M_int = M;
@@ -860,6 +864,7 @@ int pyro_sw_graph_init(pyro_sw_graph **out, int64_t n_sites, int64_t n_bonds, co
     d.NB = n_bonds;
     d.n_cross = n_bonds - n_inside;
     d.window = kWindow;
+    d.acc_lines = nwin > 1 ? kAccLines : 1;
     d.n = model;
     d.ba = (const int32_t *)(g->mem + off[0]);
     d.bb = (const int32_t *)(g->mem + off[1]);
