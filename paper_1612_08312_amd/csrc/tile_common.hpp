@@ -997,6 +997,7 @@ __device__ __forceinline__ void unite_tile_pairs(int32_t *lab, int *head, int64_
         S.direct = 0;
         S.nlost = 0;
     }
+    if (n == 0) return;  // the same in every thread
     __syncthreads();
     const int *words = head - (int64_t)tile_words;  // start of the list array, which port names index
     auto name_key = [&](int name) { return name < 0 ? (name & INT32_MAX) : words[name]; };
@@ -1273,9 +1274,12 @@ __device__ __forceinline__ void write_pending_record(const RepDesc &d, int model
     else write_pending_record<3>(d, st, ntiles, tid, with_energy, e_at, e_n, red);
 }
 
-// The unite pass of a chain: one workgroup per tile, and one per replica (the
-// last of the grid) that writes the record of the previous sweep, whose sums
-// are complete by now, and the state for the settle-and-flip pass.  A kernel
+// The unite pass of a chain: one workgroup per replica that writes the record
+// of the previous sweep, whose sums are complete by now, and the state for the
+// settle-and-flip pass, and one per tile.  The record's serial loads take 15 us
+// and more of a large lattice, so its block starts first: last in the grid it
+// outlasted the tiles where few bonds are active (XY L = 128 at 20 T_c 40 us,
+// first 32).  A kernel
 // of its own for the records, one workgroup per replica, had cost 4 to 5 us
 // and a launch gap per sweep, 5% to 9% of a sweep of L <= 64.  COUNT: it
 // counts its compare-and-swaps into c.counts (measurement runs).  The chains
@@ -1285,8 +1289,8 @@ template <bool COUNT>
 __device__ __forceinline__ void unite_block(Chain c, uint32_t b, UniteLds &S)
 {
     static_assert(kUniteThreads == kBlock, "the record block");
-    if ((int)b >= c.ntile_blocks) {
-        const int rep = (int)b - c.ntile_blocks;
+    if ((int)b < c.nreps) {
+        const int rep = (int)b;
         const RepDesc &d = c.desc[rep];
         const RepState st = c.state[rep][0];
         if (threadIdx.x == 0) c.state[rep][1] = st;
@@ -1295,7 +1299,7 @@ __device__ __forceinline__ void unite_block(Chain c, uint32_t b, UniteLds &S)
                                  S.BEST);
         return;
     }
-    const int blk = xcd_block(b, c.ntile_blocks);
+    const int blk = xcd_block((int)b - c.nreps, c.ntile_blocks);
     const int rep = c.tile_rep[blk];
     if (c.state[rep]->remaining <= 0) return;
     const RepDesc &d = c.desc[rep];
