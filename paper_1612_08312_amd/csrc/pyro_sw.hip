@@ -651,7 +651,8 @@ LaunchHook hook_of(Timer &tm, hipStream_t st)
 // 11 / 43, L = 12 34 / 53, L = 13 43 / 53.  Setting up costs a call of one
 // sweep more than it gains only beyond L = 12 (L = 13 with its record read:
 // 108 / 106 us).  A stream that is being captured takes the graph path, which
-// decides what the runtime makes of it.
+// decides what the runtime makes of it, and so does a device that refuses the
+// kernel its LDS.
 bool solo_resident(const pyro_sw *h, int64_t n)
 {
     if (h->model != PYRO_ISING || (h->L > 12 && (h->L > kQuadMaxL || n < 4)) || h->diluted || h->shape_chosen ||
@@ -662,7 +663,10 @@ bool solo_resident(const pyro_sw *h, int64_t n)
         (void)hipGetLastError();
         return false;
     }
-    return capture == hipStreamCaptureStatusNone;
+    if (capture != hipStreamCaptureStatusNone) return false;
+    if (prepare_resident(h->L) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
 }
 
 // Energy of the pending record (tail), then copy the ring to the host queue.

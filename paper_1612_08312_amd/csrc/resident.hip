@@ -26,6 +26,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "device_once.hpp"
 #include "device_util.hpp"
 #include "ising_cell.hpp"
 #include "kernels.hpp"
@@ -557,38 +558,72 @@ __global__ __launch_bounds__(kResidentThreads) void k_quad_ising(Chain c, RepSta
     if (tid == 0) c.state[rep][0] = RepState{st.t + (uint32_t)st.remaining, 0, st.ring_used + st.remaining, -1};
 }
 
-template <int PASSES>
-static hipError_t launch_quad(const Chain &c, int maxL, const RepState &armed, bool use_armed, hipStream_t st)
+// Threads of the quad kernel's instances cover that many tetrahedra each.
+static int quad_passes(int maxL)
 {
-    static const hipError_t attr = hipFuncSetAttribute((const void *)k_quad_ising<PASSES>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                       (int)quad_layout(kQuadMaxL).total);
-    if (attr != hipSuccess) return attr;
-    k_quad_ising<PASSES><<<c.nreps, kResidentThreads, quad_layout(maxL).total, st>>>(c, armed, use_armed);
-    return hipSuccess;
+    const int p = (4 * maxL * maxL * maxL + kResidentThreads - 1) / kResidentThreads;
+    return p <= 1 ? 1 : p <= 2 ? 2 : p <= 4 ? 4 : p <= 7 ? 7 : 9;
+}
+
+// Let a kernel take as much dynamic LDS as it may need, on the current device.
+static hipError_t allow_lds(const void *kernel, size_t bytes, DeviceOnce &done)
+{
+    int dev = -1;
+    const hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    return done.run(dev, [&] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes); });
+}
+
+template <int PASSES>
+static hipError_t allow_quad()
+{
+    static DeviceOnce done;
+    return allow_lds((const void *)k_quad_ising<PASSES>, quad_layout(kQuadMaxL).total, done);
+}
+
+hipError_t prepare_resident(int maxL)
+{
+    if (maxL > kQuadMaxL) {
+        static DeviceOnce done;
+        return allow_lds((const void *)k_resident_ising, resident_layout(kResidentMaxL).total, done);
+    }
+    switch (quad_passes(maxL)) {
+    case 1: return allow_quad<1>();
+    case 2: return allow_quad<2>();
+    case 4: return allow_quad<4>();
+    case 7: return allow_quad<7>();
+    default: return allow_quad<9>();
+    }
+}
+
+template <int PASSES>
+static void launch_quad(const Chain &c, int maxL, const RepState &from, bool armed, hipStream_t st)
+{
+    k_quad_ising<PASSES><<<c.nreps, kResidentThreads, quad_layout(maxL).total, st>>>(c, from, armed);
 }
 
 hipError_t launch_resident_ising(const Chain &c, int maxL, const RepState *armed, hipStream_t st, const LaunchHook &hook)
 {
     if (c.nreps == 0) return hipSuccess;
     if (maxL < 1 || maxL > kResidentMaxL || (armed && c.nreps != 1)) return hipErrorInvalidValue;
+    const hipError_t e = prepare_resident(maxL);
+    if (e != hipSuccess) return e;
     const RepState from = armed ? *armed : RepState{};
-    const int tets = 4 * maxL * maxL * maxL, passes = (tets + kResidentThreads - 1) / kResidentThreads;
-    hipError_t e = hipSuccess;
+    const bool use = armed != nullptr;
     if (hook.before) hook.before(hook.ctx, kKResident);
     if (maxL > kQuadMaxL) {
-        static const hipError_t attr = hipFuncSetAttribute(
-            (const void *)k_resident_ising, hipFuncAttributeMaxDynamicSharedMemorySize, (int)resident_layout(kResidentMaxL).total);
-        e = attr;
-        if (e == hipSuccess)
-            k_resident_ising<<<c.nreps, kResidentThreads, resident_layout(maxL).total, st>>>(c, from, armed != nullptr);
-    } else if (passes <= 1) e = launch_quad<1>(c, maxL, from, armed != nullptr, st);
-    else if (passes <= 2) e = launch_quad<2>(c, maxL, from, armed != nullptr, st);
-    else if (passes <= 4) e = launch_quad<4>(c, maxL, from, armed != nullptr, st);
-    else if (passes <= 7) e = launch_quad<7>(c, maxL, from, armed != nullptr, st);
-    else e = launch_quad<9>(c, maxL, from, armed != nullptr, st);
+        k_resident_ising<<<c.nreps, kResidentThreads, resident_layout(maxL).total, st>>>(c, from, use);
+    } else {
+        switch (quad_passes(maxL)) {
+        case 1: launch_quad<1>(c, maxL, from, use, st); break;
+        case 2: launch_quad<2>(c, maxL, from, use, st); break;
+        case 4: launch_quad<4>(c, maxL, from, use, st); break;
+        case 7: launch_quad<7>(c, maxL, from, use, st); break;
+        default: launch_quad<9>(c, maxL, from, use, st);
+        }
+    }
     if (hook.after) hook.after(hook.ctx, kKResident);
-    return e == hipSuccess ? hipGetLastError() : e;
+    return hipGetLastError();
 }
 
 }  // namespace pyro

@@ -61,6 +61,10 @@ __host__ __device__ inline QuadLayout quad_layout(int L)
     return r;
 }
 
+// Let the kernels for edges up to maxL take their LDS on the current device
+// (done once per device; a failure is not kept).
+hipError_t prepare_resident(int maxL);
+
 // All `remaining` sweeps of every replica of the chain (each of edge
 // L <= kResidentMaxL, no vacant site), one workgroup per replica, with the
 // dynamic LDS of the largest edge maxL.  armed: the state to start from in
