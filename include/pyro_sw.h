@@ -279,7 +279,9 @@ int pyro_sw_group_destroy(pyro_sw_group *g);
  * <= 136, larger): each lane is one group (pyro_sw_group_*) on its own
  * stream, advanced a quantum at a time, the quantum being as many group
  * sweeps as fit in quantum_ms by the lane's measured sweep time (each member
- * runs at most its remaining sweeps).  Lanes overlap on the device.  Jobs
+ * runs at most its remaining sweeps).  Lanes overlap on the device.  A lane's
+ * stream is made with its first job; if that fails, the job ends with
+ * PYRO_EDEVICE and the next one tries again.  Jobs
  * join and leave a lane between its quanta, so work that arrives while
  * other jobs run starts as soon as a slot and memory free up (continuous
  * batching).  Every job's records and final spins are identical to a plain

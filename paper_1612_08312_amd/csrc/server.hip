@@ -193,21 +193,34 @@ int admit(pyro_sw_server *s, bool *progress)
             head = false;
             continue;
         }
+        auto reject = [&](int rc) {  // the job ends here; the others go on
+            s->arena.release(off);
+            j->error = rc;
+            j->state = PYRO_JOB_DONE;
+            j->t_admit = j->t_done = s->now();
+            it = s->queue.erase(it);
+        };
         // A lane's stream is made when its first job comes: a process has four
-        // hardware queues, and two lanes on one queue do not overlap.
-        if (!ln.st && hipStreamCreateWithFlags(&ln.st, hipStreamNonBlocking) != hipSuccess)
-            return server_fail(s, PYRO_EDEVICE, "lane stream creation failed");
+        // hardware queues, and two lanes on one queue do not overlap.  Nothing
+        // runs on a lane without one, so a stream that cannot be made fails the
+        // job, not the server.
+        if (!ln.st && hipStreamCreateWithFlags(&ln.st, hipStreamNonBlocking) != hipSuccess) {
+            (void)hipGetLastError();
+            ln.st = nullptr;
+            reject(PYRO_EDEVICE);
+            *progress = true;
+            continue;
+        }
         pyro_sw *h = nullptr;
         const int rc = pyro_sw_init_ext(&h, j->spec.L, j->spec.model, j->spec.T, j->spec.J, j->spec.seed,
                                         j->spec.start, ln.st, s->base + off, j->spin_bytes,
                                         s->base + off + j->spin_bytes, j->work_bytes);
         if (rc) {
-            s->arena.release(off);
-            if (rc == PYRO_EDEVICE) return server_fail(s, rc, "job initialisation failed on the device");
-            j->error = rc;
-            j->state = PYRO_JOB_DONE;
-            j->t_admit = j->t_done = s->now();
-            it = s->queue.erase(it);
+            if (rc == PYRO_EDEVICE) {
+                s->arena.release(off);
+                return server_fail(s, rc, "job initialisation failed on the device");
+            }
+            reject(rc);
             continue;
         }
         j->h = h;
