@@ -156,6 +156,7 @@ __device__ __forceinline__ void on_tile_pass(Chain c, int blk, OnTileLds<TX * TY
         for (int qg = 0; qg < 12; ++qg) {
             float xs[4];
             bool any = false;
+            double e4 = 0.0;  // energy of these four bonds: added up at their own size, then once to the cell's
 #pragma unroll
             for (int k4 = 0; k4 < 4; ++k4) {
                 const int j = 4 * qg + k4;
@@ -169,9 +170,10 @@ __device__ __forceinline__ void on_tile_pass(Chain c, int blk, OnTileLds<TX * TY
                 for (int k = 0; k < NV; ++k) {
                     const float va = tet < 4 ? own[k][ia] : dv[k][ia];
                     const float vb = tet < 4 ? own[k][ib] : dv[k][ib];
-                    esum = __fma_rn((double)va, (double)vb, esum);
+                    e4 = __fma_rn((double)va, (double)vb, e4);
                 }
             }
+            esum += e4;
             if (any) {
                 const uint4 rnd = philox4x32_10(12u * (uint32_t)cell + qg, st.t, kStreamBond, 0u, d.key);
                 // the four filters without a branch; one for the rare close calls
