@@ -454,53 +454,63 @@ def graph_throughput(sweeps, stream, dev):
     return out
 
 
-def kernel_bounds(kt, N, cas_per_launch, hooks_per_launch, cas_ceiling, copy_gbs, counters_valid):
-    """Each Ising pass of one L=128 lattice (per-sweep launches, mean over the
-    probe): its duration, what bounds it, and the fraction of that bound it
-    reaches.  The tile pass is bound by VALU issue (wave instructions per
-    launch from the counters / duration, against one wave instruction per CU
-    and cycle); the settle-and-flip pass by HBM streaming (counter bytes /
-    duration, against 8 TB/s and the measured copy bandwidth: its 6 B/site
-    of labels and spins plus the settle step's walks) and by the latency of
-    its settle walks; the
-    unite pass by device atomics
-    (compare-and-swaps per launch / duration, against the measured random
-    compare-and-swap rate); the finalize (at drains only: the unite
-    pass writes the records) by launch latency (one workgroup per lattice).  There is no store pass: each tile settles its own hooked
-    roots at the start of its flip."""
+def launch_traffic(kernel, lattices, counters_valid):
+    """HBM bytes of one launch of a kernel over `lattices` L=128 lattices from
+    the counters (per lattice), or None without valid ones."""
+    return MEASURED_TRAFFIC[kernel] * lattices if counters_valid and kernel in MEASURED_TRAFFIC else None
+
+
+def kernel_bounds(kt, N, lattice_sweeps, cas_per_lattice, hooks_per_lattice, cas_ceiling, copy_gbs, counters_valid):
+    """Each Ising pass of a probe of `lattice_sweeps` L=128 lattice sweeps
+    (per-sweep launches, one per slice of the group; kt: launches and ms of
+    each kernel): its mean duration and how many lattices a launch covers,
+    what bounds it, and the fraction of that bound it reaches.  The tile pass
+    is bound by VALU issue (wave instructions per lattice from the counters /
+    duration, against one wave instruction per CU and cycle); the
+    settle-and-flip pass by HBM streaming (counter bytes / duration, against
+    8 TB/s and the measured copy bandwidth: its 6 B/site of labels and spins
+    plus the settle step's walks) and by the latency of its settle walks; the
+    unite pass by device atomics (compare-and-swaps per launch / duration,
+    against the measured random compare-and-swap rate).  There is no store
+    pass: each tile settles its own hooked roots at the start of its flip, and
+    the unite pass writes the records."""
     out = {}
     for k, (n, ms) in kt.items():
         if not n:
             continue
         us = ms / n * 1e3
+        lat = lattice_sweeps / n  # lattices that one launch covers, on the mean
         row = {"us": round(us, 2)}
+        if k in ("local", "unite", "flip"):
+            row["lattices_per_launch"] = lat
         if k == "local":
             row["bound"] = "VALU issue"
             if counters_valid and k in MEASURED_ISSUE:
                 valu, salu, waves = MEASURED_ISSUE[k]
                 row.update(valu_per_wave=round(valu / waves), salu_per_wave=round(salu / waves),
-                           achieved_wave_instr_per_s=valu / (us * 1e-6), peak_wave_instr_per_s=VALU_ISSUE_PEAK,
-                           frac=valu / (us * 1e-6) / VALU_ISSUE_PEAK)
-            row["hbm_alg_frac"] = 5.0 * N / (us * 1e-6) / (HBM_PEAK_GBS * 1e9)
+                           achieved_wave_instr_per_s=valu * lat / (us * 1e-6), peak_wave_instr_per_s=VALU_ISSUE_PEAK,
+                           frac=valu * lat / (us * 1e-6) / VALU_ISSUE_PEAK)
+            row["hbm_alg_frac"] = 5.0 * N * lat / (us * 1e-6) / (HBM_PEAK_GBS * 1e9)
         elif k == "unite":
-            row.update(bound="device atomics", cas_per_launch=round(cas_per_launch),
-                       hooks_per_launch=round(hooks_per_launch), achieved_cas_per_s=cas_per_launch / (us * 1e-6),
-                       peak_cas_per_s=cas_ceiling, frac=cas_per_launch / (us * 1e-6) / cas_ceiling)
+            cas = cas_per_lattice * lat
+            row.update(bound="device atomics", cas_per_launch=round(cas), hooks_per_launch=round(hooks_per_lattice * lat),
+                       achieved_cas_per_s=cas / (us * 1e-6), peak_cas_per_s=cas_ceiling,
+                       frac=cas / (us * 1e-6) / cas_ceiling)
         elif k == "flip":
             row["bound"] = "HBM streaming (labels and spins) and the settle step's walk latency"
-            row.update(alg_bytes_per_site=6.0, hbm_alg_frac=6.0 * N / (us * 1e-6) / (HBM_PEAK_GBS * 1e9))
-            if counters_valid and k in MEASURED_TRAFFIC:
-                gbs = MEASURED_TRAFFIC[k] / (us * 1e-6) / 1e9
+            row.update(alg_bytes_per_site=6.0, hbm_alg_frac=6.0 * N * lat / (us * 1e-6) / (HBM_PEAK_GBS * 1e9))
+            if launch_traffic(k, lat, counters_valid) is not None:
+                gbs = launch_traffic(k, lat, counters_valid) / (us * 1e-6) / 1e9
                 row.update(achieved_GBps=gbs, peak_GBps=HBM_PEAK_GBS, frac=gbs / HBM_PEAK_GBS,
                            frac_of_copy=gbs / copy_gbs)
             if counters_valid and k in MEASURED_ISSUE:
                 valu, salu, waves = MEASURED_ISSUE[k]
                 row.update(valu_per_wave=round(valu / waves), salu_per_wave=round(salu / waves),
-                           valu_issue_frac=valu / (us * 1e-6) / VALU_ISSUE_PEAK)
+                           valu_issue_frac=valu * lat / (us * 1e-6) / VALU_ISSUE_PEAK)
         elif k == "finalize":
             row["bound"] = "launch latency (one workgroup per lattice)"
-        if counters_valid and k in MEASURED_TRAFFIC:
-            row["counter_bytes_per_launch"] = MEASURED_TRAFFIC[k]
+        if k in ("local", "unite", "flip") and launch_traffic(k, lat, counters_valid) is not None:
+            row["counter_bytes_per_launch"] = launch_traffic(k, lat, counters_valid)
         out[k] = row
     return out
 
@@ -514,7 +524,7 @@ def main():
     ap.add_argument("--cpu-sweeps", type=int, default=4, help="oracle sweeps for cpu_baseline (0: skip)")
     ap.add_argument("--tile-shape", type=int, default=-1, help="tile shape id (-1: autotune)")
     ap.add_argument("--slices", type=int, default=0,
-                    help="concurrent slices of the five-lattice group (0: the group's default, one per lattice)")
+                    help="concurrent slices of the five-lattice group (0: the group's default)")
     ap.add_argument("--cas-count-sweeps", type=int, default=4,
                     help="sweeps of the unite-pass counting run (0: skip; it adds one atomic per swap)")
     ap.add_argument("--ising-mode", choices=("auto", "graph", "persistent"), default="auto",
@@ -594,7 +604,8 @@ def main():
     saved_mode = group.mode()
     group.set_mode(pyrosw.PYRO_MODE_GRAPH, saved_mode[1])
     pyrosw.pyro_sw_group_set_timing(group.g, -1)
-    group.sweep(10)
+    probe_sweeps = 10
+    group.sweep(probe_sweeps)
     kt = {k: list(v) for k, v in pyrosw.pyro_sw_group_kernel_times(group.g).items()}
     pyrosw.pyro_sw_group_set_timing(group.g, 0)
     group.set_mode(*saved_mode)
@@ -610,7 +621,7 @@ def main():
     dom_n, dom_ms = pyrosw.pyro_sw_group_kernel_times(group.g)[dominant]
     pyrosw.pyro_sw_group_set_timing(group.g, 0)
 
-    # Compare-and-swaps of the unite pass per launch (a counting run of
+    # Compare-and-swaps of the unite pass per lattice (a counting run of
     # per-sweep launches: one more atomic per swap, so it is not timed) and
     # the device's random compare-and-swap ceiling on a label-sized array.
     count_sweeps = args.cas_count_sweeps
@@ -645,7 +656,7 @@ def main():
     bytes_per_launch = byte_model.get(dominant, 0.0) * N * len(lats) / launches_per_step
     achieved = bytes_per_launch / dom_avg_s / 1e9 if dom_avg_s > 0 else 0.0
     counters_valid = COUNTER_FINGERPRINT == kernel_fingerprint()
-    traffic = MEASURED_TRAFFIC.get(dominant) if counters_valid and launches_per_step == len(lats) else None
+    traffic = launch_traffic(dominant, len(lats) / launches_per_step, counters_valid)
     binder, binder_all = {}, {}
     for T, r in zip(temps, recs):
         half = r[len(r) // 2:]
@@ -676,7 +687,7 @@ def main():
             "sweeps_per_lattice": args.steps,
             "step": ("one SW sweep of each lattice (every sweep of the timed call in one persistent launch)"
                      if ising_mode == "persistent" else
-                     "one SW sweep of each lattice (one captured graph per lattice and sweep, run concurrently)"),
+                     "one SW sweep of each lattice (one captured graph per slice of the group and sweep, slices run concurrently)"),
             "tile_shape": shape,
             "ising_mode": ising_mode,
         },
@@ -705,7 +716,7 @@ def main():
             "fold": philox_fold,
         },
         "sweep_alg_roofline_frac": value * SWEEP_BYTES_PER_SITE / (HBM_PEAK_GBS * 1e9),
-        "kernels": kernel_bounds(kt, N, cas_tried / max(count_sweeps * len(lats), 1),
+        "kernels": kernel_bounds(kt, N, probe_sweeps * len(lats), cas_tried / max(count_sweeps * len(lats), 1),
                                  cas_hooked / max(count_sweeps * len(lats), 1), cas_ceiling, copy_gbs, counters_valid),
         "binder_U_second_half": binder,
         "binder_U_all_sweeps": binder_all,
