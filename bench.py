@@ -50,23 +50,22 @@ def bytes_per_site(shape):
     }
 
 
-# Per-launch counter figures of the Ising kernels (one L=128 lattice, 8x8x8
+# Counter figures of the Ising kernels (per launch over one L=128 lattice, 8x8x8
 # tiles) from rocprofv3 --pmc runs of `bench.py --pmc-probe`: HBM bytes
 # (FETCH_SIZE and WRITE_SIZE, each scaled by the same counter's reading for
 # the probe's 256 MiB copy) and wave instructions (SQ_INSTS_VALU,
 # SQ_INSTS_SALU, SQ_WAVES).  Valid only for the kernel sources they were
 # taken with (fingerprint); the summaries are in profiles/.
-COUNTER_FINGERPRINT = "bce8deb94f4062c8"
-MEASURED_TRAFFIC = {  # kernel -> HBM bytes per launch
-    "local": 216857639,
-    "unite": 194594163,
-    "flip": 269545072,
-    "finalize": 73136,
+COUNTER_FINGERPRINT = "a282260c778a761b"
+MEASURED_TRAFFIC = {  # kernel -> HBM bytes per lattice
+    "local": 229462194,
+    "unite": 140844027,
+    "flip": 269442635,
 }
-MEASURED_ISSUE = {  # kernel -> (VALU wave instructions, SALU wave instructions, waves) per launch
-    "local": (62134795, 28267641, 32768),
-    "unite": (11532870, 12803987, 16384),
-    "flip": (24889449, 10496674, 32768),
+MEASURED_ISSUE = {  # kernel -> (VALU wave instructions, SALU wave instructions, waves) per lattice
+    "local": (51854612, 22551384, 32768),
+    "unite": (11742642, 13000027, 16388),
+    "flip": (24623226, 10648012, 32768),
 }
 
 # Issue ceiling of the vector ALUs: a wave64 VALU instruction occupies a
