@@ -396,7 +396,7 @@ int pyro_sw_atomic_rate(int mode, int64_t words, int64_t ops, int repeats, doubl
  *                          pyro_sw_init.  One device allocation: 12 B per
  *                          bond (ends and table position) and 4 B more per
  *                          bond inside a window (512 to 4096 sites, by
- *                          n_sites; Ising: 2 B more, and 4 B per distinct
+ *                          n_sites and the bonds; Ising: 2 B more, and 4 B per distinct
  *                          random block of a window's bonds, when a block
  *                          serves two bonds or more), spins, 4 B per
  *                          site of labels (O(n): 4 more of projections; 4

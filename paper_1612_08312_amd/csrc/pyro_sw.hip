@@ -113,8 +113,10 @@ constexpr int kMaxSlices = 8;  // concurrent slices of a group
 // latency and atomics, run beside the other's arithmetic; more only cut the
 // launches smaller, and past four they share hardware queues.  Per sweep with
 // 1 / 2 / 4 / 8 slices: five L = 128 lattices (five at most) 1.33 / 1.33 /
-// 1.34 / 1.34 ms, 48 Ising replicas of L = 8 to 48 460 / 446 / 486 / 527 us,
-// 27 Heisenberg lattices of L = 24 to 48 633 / 609 / 609 / 599 us.
+// 1.34 / 1.34 ms, 48 Ising replicas of L = 8 to 48 460 / 446 / 486 / 527 us.
+// O(n) the same: Heisenberg, 27 of L = 24 to 48 427 / 397 / 391 / 376 us, 48 of
+// L = 24 227 / 197 / 201 / 239, eight of L = 64 592 / 556 / 558 / 564; XY 351 /
+// 312 / 314 / 317, 205 / 179 / 188 / 225, 494 / 452 / 451 / 435.
 // A group of few sites runs in one: its launches leave the chip idle as they
 // are, and a second stream doubles them.  With 1 / 2 slices: two Ising lattices
 // of L = 48 (3.5 M sites) 79 / 87 us, two of L = 64 (8.4 M) 119 / 112 us; XY

@@ -1218,7 +1218,9 @@ __device__ __forceinline__ void unite_tile(const RepDesc &d, int tile, int tid, 
 
 // ------------------------------------------------------------- records ---
 // The record of the last sweep (ring slot st.e_pending, sweep st.t - 1): its
-// magnetisation from the ntiles partials of that sweep's settle-and-flip pass, its
+// magnetisation from the ntiles partials of that sweep's settle-and-flip pass,
+// which therefore has to be the last sweep the lattice had (LDS-resident sweeps
+// leave no record pending), its
 // energy from the partials at e_at (the next tile pass, whose tiles count the
 // energy of the state entering the sweep, or the energy tail), in an order
 // fixed by the block size.  with_energy = false leaves the energy to a later
